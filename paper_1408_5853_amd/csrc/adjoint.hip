@@ -34,12 +34,10 @@ namespace cryo {
 
 constexpr int ADJ_WAVES = 8;
 
-// pass 1 keeps per-row sums in LDS after the law and row tables
-__host__ __device__ inline size_t adj_acc_offset(int L, int np) {
-    return ring_lds_offset<double>(L, np);
-}
-__host__ __device__ inline size_t adj_lds_bytes(int L, int np, int rpl) {
-    return adj_acc_offset(L, np) + 2 * (size_t)ADJ_WAVES * rpl * WAVE * sizeof(double);
+// pass 1 keeps per-row sums in LDS after the tables
+__host__ __device__ inline size_t adj_lds_bytes(int L, int np, int rpl, bool poly, bool stepped) {
+    return tables_bytes<double>(L, np, poly, stepped) +
+           2 * (size_t)ADJ_WAVES * rpl * WAVE * sizeof(double);
 }
 
 // exchange of one value per lane with the neighbouring lanes of the line
@@ -60,8 +58,8 @@ __device__ inline void nb_exchange(double v_last, double v_first, double &from_p
 }
 
 // Row tables and laws in LDS (dynamic shared memory); all threads call it.
-// STEPPED (eq. (9)): the terminal lines' tables too, after the row sums
-// (sgw2, sge2, sinf2; the full lines' tables otherwise).
+// STEPPED (eq. (9)): the terminal lines' tables too (sgw2, sge2, sinf2; the
+// full lines' tables otherwise).
 // POLY: the polynomial laws of eqs. (23), (24) (the stepping kernel's
 // coefficient blob) instead of the power tables.
 template <bool POLY>
@@ -70,35 +68,23 @@ struct AdjLds {
     const uint32_t *sinf;
     const double *sgw2, *sge2;
     const uint32_t *sinf2;
+    double *sums;                     // the row sums, after the tables
     std::conditional_t<POLY, LawPoly<double>, LawLds<double>> law;
 };
 template <bool STEPPED, bool POLY = false>
-__device__ inline AdjLds<POLY> adj_stage(const StepArgs<double> &a, unsigned char *smem, int rpl) {
-    double *sgw = (double *)(smem + ((law_lds_bytes<double>(a.laws.L) + 15) & ~(size_t)15));
-    double *sge = sgw + a.np;
-    uint32_t *sinf = (uint32_t *)(sge + a.np);
-    double *sgw2 = (double *)(smem + adj_lds_bytes(a.laws.L, a.np, rpl));
-    double *sge2 = sgw2 + a.np;
-    uint32_t *sinf2 = (uint32_t *)(sge2 + a.np);
-    for (int i = threadIdx.x; i < a.np; i += blockDim.x) {
-        sgw[i] = a.gw[i];
-        sge[i] = a.ge[i];
-        sinf[i] = a.info[i];
-        if constexpr (STEPPED) {
-            sgw2[i] = a.gw2[i];
-            sge2[i] = a.ge2[i];
-            sinf2[i] = a.info2[i];
-        }
-    }
+__device__ inline AdjLds<POLY> adj_stage(const StepArgs<double> &a, unsigned char *smem) {
+    const size_t tbytes = tables_bytes<double>(a.L, a.np, POLY, STEPPED);
+    stage_tables(a.img, smem, (unsigned)tbytes);
     AdjLds<POLY> t;
-    t.sgw = sgw;
-    t.sge = sge;
-    t.sinf = sinf;
-    t.sgw2 = STEPPED ? sgw2 : sgw;
-    t.sge2 = STEPPED ? sge2 : sge;
-    t.sinf2 = STEPPED ? sinf2 : sinf;
-    if constexpr (POLY) t.law = stage_poly<double>(a, smem);   // ends with a barrier
-    else t.law = stage_laws<double>(a, smem);
+    t.sgw = (const double *)(smem + law_bytes<double>(a.L, POLY));
+    t.sge = t.sgw + a.np;
+    t.sinf = (const uint32_t *)(t.sge + a.np);
+    t.sgw2 = (const double *)((const unsigned char *)t.sgw + (STEPPED ? row_bytes<double>(a.np) : 0));
+    t.sge2 = t.sgw2 + a.np;
+    t.sinf2 = (const uint32_t *)(t.sge2 + a.np);
+    t.sums = (double *)(smem + tbytes);
+    t.law = staged_laws<double, POLY>(smem, a.L);
+    stage_wait();
     return t;
 }
 
@@ -131,7 +117,7 @@ template <int RPL, int G, bool CUBE, bool STEPPED = false, bool POLY = false>
 // heater row's source is X sqrt(tref / T) at the old T (a.jsq holds
 // sqrt(tref)).
 __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
-                                 unsigned char *smem, const AdjLds<POLY> &tb,
+                                 const AdjLds<POLY> &tb,
                                  const double (&lamR)[RPL], bool keep) {
     constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
     __shared__ double xchg[NG][9 * G];
@@ -149,7 +135,7 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
     const int qE = lg < NL - 1 ? lg + 1 : (RPL - 1) * NL + lg;
     const double cS = d.cS ? *d.cS : 0.0;                    // dJ/dS of this state
     // per-row sums over the group's lines, in LDS (registers): [wave][row][lane]
-    double *accW = (double *)(smem + adj_acc_offset(a.laws.L, a.np)) + (size_t)wv * RPL * WAVE + lane;
+    double *accW = tb.sums + (size_t)wv * RPL * WAVE + lane;
     double *accE = accW + (size_t)ADJ_WAVES * RPL * WAVE;
     double gS = 0.0;
 #pragma unroll
@@ -202,7 +188,7 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
             // west coefficient is the ratio law at the node and its east one
             // h_i; boundary rows have their unit or zero laws folded into gw,
             // ge (slot 2 is the unit law there, the zero law on padding)
-            double l2v = l2 == law_unit(a.laws.L) ? 1.0 : 0.0;
+            double l2v = l2 == law_unit(a.L) ? 1.0 : 0.0;
             if (__any(ifc)) {
                 double va = law.lawc(l2, t);
                 if constexpr (POLY) va = va / law.lawc((inf_r >> 18) & 63, t);
@@ -371,9 +357,9 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
     __syncthreads();
     // this workgroup's running sums (one slot per workgroup: no other writer),
     // its line groups added in a fixed order
-    const double *accL = (const double *)(smem + adj_acc_offset(a.laws.L, a.np));
+    const double *accL = tb.sums;
     double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np;
-    for (int q = threadIdx.x; q < a.np; q += blockDim.x) {
+    for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
         const int r = q / NL, lq = q % NL, w0 = lq / WAVE, ln = lq % WAVE;
         double sw = 0.0, se = 0.0;
         for (int g = 0; g < NG; ++g) {
@@ -395,9 +381,9 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
 template <int RPL, int G, bool CUBE, bool STEPPED, bool POLY = false>
 __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj1(StepArgs<double> a, AdjArgs d) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem, RPL);
+    const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem);
     const double none[RPL] = {};
-    adj1_body<RPL, G, CUBE, STEPPED, POLY>(a, d, smem, tb, none, false);
+    adj1_body<RPL, G, CUBE, STEPPED, POLY>(a, d, tb, none, false);
 }
 
 // Pass 2: axial faces.  Each interior line j adds the terms of its two
@@ -407,7 +393,7 @@ template <int RPL, int G, bool STEPPED = false, bool POLY = false>
 // (keep: lam^n of the group's single line goes to lamR, not to memory; the
 // boundary lines' lam^n is always written)
 __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
-                                 unsigned char *smem, const AdjLds<POLY> &tb,
+                                 const AdjLds<POLY> &tb,
                                  double (&lamR)[RPL], bool keep) {
     constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
     const uint32_t *sinf = tb.sinf;                      // this line's table
@@ -434,7 +420,7 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
         const int q = r * NL + lg;
         const uint32_t inf_r = sinf[q];
         const bool cap = (inf_r & 7) == K_CAP;
-        const int lz = cap ? (inf_r >> 12) & 63 : law_zero(a.laws.L);
+        const int lz = cap ? (inf_r >> 12) & 63 : law_zero(a.L);
         const double t = d.T[bb + q], ts = d.T[bb - LS + q];
         const double y = d.Y[bb + q];
         const double fs = 0.5 * (t + ts);
@@ -477,7 +463,7 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
             if constexpr (STEPPED)
                 if (j == a.z_full && (tb.sinf2[q] & 7) != K_CAP) cap = false;
             // non-capacity rows take the zero law: every face term vanishes
-            const int lz = cap ? (inf_r >> 12) & 63 : law_zero(a.laws.L);
+            const int lz = cap ? (inf_r >> 12) & 63 : law_zero(a.L);
             const double t = Tc[r], tn = Tn[r];
             const double y = Yc[r], yn = Yn[r], ys = Ys[r];
             // north face (j, j+1); the south face (j-1, j) is carried
@@ -512,12 +498,12 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
         }
     }
     // this workgroup's sums, its line groups added in a fixed order
-    double *accL = (double *)(smem + adj_acc_offset(a.laws.L, a.np));
+    double *accL = tb.sums;
 #pragma unroll
     for (int r = 0; r < RPL; ++r) accL[(size_t)wv * RPL * WAVE + r * WAVE + lane] = accZ[r];
     __syncthreads();
     double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np + 2 * a.np;
-    for (int q = threadIdx.x; q < a.np; q += blockDim.x) {
+    for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
         const int r = q / NL, lq = q % NL, w0 = lq / WAVE, ln = lq % WAVE;
         double sz = 0.0;
         for (int g = 0; g < NG; ++g)
@@ -529,9 +515,9 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
 template <int RPL, int G, bool STEPPED, bool POLY = false>
 __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj2(StepArgs<double> a, AdjArgs d) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem, RPL);
+    const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem);
     double lamR[RPL];
-    adj2_body<RPL, G, STEPPED, POLY>(a, d, smem, tb, lamR, false);
+    adj2_body<RPL, G, STEPPED, POLY>(a, d, tb, lamR, false);
 }
 
 // Pass 2 of step k and pass 1 of step k - 1 in one launch: each line group
@@ -544,13 +530,13 @@ template <int RPL, int G, bool CUBE, bool KEEP, bool STEPPED, bool POLY = false>
 __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj21(StepArgs<double> a, AdjArgs d2,
                                                            AdjArgs d1) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem, RPL);
+    const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem);
     // one line per group: lam^k stays in registers between the phases (no
     // other group reads it)
     double lamR[RPL] = {};
-    adj2_body<RPL, G, STEPPED, POLY>(a, d2, smem, tb, lamR, KEEP);
+    adj2_body<RPL, G, STEPPED, POLY>(a, d2, tb, lamR, KEEP);
     __syncthreads();           // the LDS row sums area passes to the next phase
-    adj1_body<RPL, G, CUBE, STEPPED, POLY>(a, d1, smem, tb, lamR, KEEP);
+    adj1_body<RPL, G, CUBE, STEPPED, POLY>(a, d1, tb, lamR, KEEP);
 }
 
 // lam^N = dJ_N / dT^N: the surface weights on the outer row
@@ -589,10 +575,13 @@ int adj_grid(const cryo_plan *p) {
 // row-sum slots: one per workgroup of the adjoint passes
 int adj_slots(const cryo_plan *p) { return adj_grid(p); }
 
-// dynamic LDS of the adjoint passes (a stepped domain adds the terminal's
-// tables)
+// dynamic LDS of the adjoint passes, and what a plan is accepted against
+// (power tables whatever its laws)
 size_t adj_lds(const cryo_plan *p) {
-    return adj_lds_bytes(p->L, p->np, p->rpl) + (p->stepped ? step_tables_bytes<double>(p->np) : 0);
+    return adj_lds_bytes(p->L, p->np, p->rpl, p->poly, p->stepped);
+}
+size_t adj_lds_reserve(const cryo_plan *p) {
+    return adj_lds_bytes(p->L, p->np, p->rpl, false, p->stepped);
 }
 
 StepArgs<double> step_args_f64(const cryo_plan *p, int *flag);
@@ -635,7 +624,7 @@ cryo_status launch_adj(const cryo_plan *p, int pass, const AdjArgs &d, int *flag
     const size_t lds = adj_lds(p);
     const int key = p->rpl * 10 + p->wpl;
     if (pass == 21 && !d1) return fail(CRYO_ERR_ARG, "fused adjoint passes need two steps");
-    const bool cube = a.laws.cube, keep = a.lpw == 1;
+    const bool cube = a.cube, keep = a.lpw == 1;
 #define ADJ_CASE(R_, G_)                                                                    \
     case R_ * 10 + G_:                                                                      \
         if (p->poly && p->stepped)                                                          \

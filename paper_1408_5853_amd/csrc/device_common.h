@@ -134,10 +134,9 @@ struct StepArgs {
     const R *Tin;             // single plan: this step's input and output
     R *Tout;
     R *buf[2];                // batch: ping-pong buffers (step n reads buf[n & 1])
-    const R *gw, *ge;         // per-row tables: west/east geometry factors
-    const uint32_t *info;
-    const double *pow_blob;   // FP64 power tables (device)
-    Laws laws;
+    const unsigned char *img; // table image (tables_bytes), staged in LDS
+    int L;                    // layers
+    int cube;                 // every capacity exponent is 3
     int nz, np;
     int lpw;                  // lines per wave (a contiguous block)
     R X;                      // amplitude * pulse average of this step
@@ -153,8 +152,6 @@ struct StepArgs {
     // stepped domain (eq. (9)): lines above z_full take the terminal's row
     // tables (nz - 1 when there is none)
     int z_full;
-    const R *gw2, *ge2;
-    const uint32_t *info2;
     double jsq;               // sqrt(T_J) with the Joule source, else 1 (batch
                               // and adjoint kernels form their source with it)
 };
@@ -387,28 +384,29 @@ __device__ inline R dif(R ah, R al, R bh, R bl) {
         return ah - bh;
 }
 
-// LDS bytes of the staged tables: laws, then per-row gw, ge, info
+// The tables of a plan as the kernels hold them in LDS, and as the device
+// keeps them (one image, copied in at the start of a launch): the laws, then
+// the rows' gw, ge, info, then for a stepped domain the terminal's.
+__host__ __device__ constexpr size_t up16(size_t b) { return (b + 15) & ~(size_t)15; }
 template <typename R>
-__host__ __device__ inline size_t law_lds_bytes(int L) {
+__host__ __device__ inline size_t law_bytes(int L, bool poly) {
     const int nlaw = 3 * L + 2;
-    if constexpr (sizeof(R) == 8)
-        return sizeof(double) * pow_blob_doubles(L);
-    else    // room for POLY_BLK floats per law id (polynomial laws)
-        return sizeof(float) * POLY_BLK * nlaw;
+    if (poly) return up16(sizeof(R) * POLY_BLK * nlaw);
+    if constexpr (sizeof(R) == 8) return up16(sizeof(double) * pow_blob_doubles(L));
+    else return up16(sizeof(float) * 4 * nlaw);        // log2 K - e, e, {K, A}
+}
+// one set of per-row tables (gw, ge, info) of an np-row line
+template <typename R>
+__host__ __device__ inline size_t row_bytes(int np) {
+    return up16((2 * sizeof(R) + sizeof(uint32_t)) * (size_t)np);
+}
+template <typename R>
+__host__ __device__ inline size_t tables_bytes(int L, int np, bool poly, bool stepped) {
+    return law_bytes<R>(L, poly) + (stepped ? 2 : 1) * row_bytes<R>(np);
 }
 // The stepping kernel also keeps a two-slot ring of line buffers per wave
 // (the lines after the current one, loaded straight into LDS): a slot is
 // RPL rows x planes x 64 lanes.
-template <typename R>
-__host__ __device__ inline size_t ring_lds_offset(int L, int np) {
-    size_t b = (law_lds_bytes<R>(L) + 15) & ~(size_t)15;
-    return (b + (2 * sizeof(R) + sizeof(uint32_t)) * (size_t)np + 15) & ~(size_t)15;
-}
-// one set of per-row tables (gw, ge, info) of an np-row line, 16-aligned
-template <typename R>
-__host__ __device__ inline size_t step_tables_bytes(int np) {
-    return ((2 * sizeof(R) + sizeof(uint32_t)) * (size_t)np + 15) & ~(size_t)15;
-}
 template <typename R>
 __host__ __device__ inline size_t ring_slot_elems(int rpl) {
     return (size_t)rpl * (Pair<R>::on ? 2 : 1) * WAVE;
@@ -428,52 +426,57 @@ __host__ __device__ constexpr bool fs_in_lds(int rpl) {
 }
 // the ring, or the FP64 carried fluxes, after the tables
 template <typename R>
-__host__ __device__ inline size_t step_lds_bytes(int L, int np, int rpl = 0) {
-    size_t extra = 0;
-    if (ring_used<R>(rpl))
-        extra = 2 * (size_t)STEP_WAVES * ring_slot_elems<R>(rpl);
-    else if (fs_in_lds<R>(rpl))
-        extra = (size_t)STEP_WAVES * rpl * WAVE;
-    return ring_lds_offset<R>(L, np) + extra * sizeof(R);
+__host__ __device__ inline size_t line_lds_bytes(int rpl) {
+    if (ring_used<R>(rpl)) return sizeof(R) * 2 * (size_t)STEP_WAVES * ring_slot_elems<R>(rpl);
+    if (fs_in_lds<R>(rpl)) return sizeof(R) * (size_t)STEP_WAVES * rpl * WAVE;
+    return 0;
 }
 
-// Stage the law tables in LDS (dynamic shared memory); all threads call it.
+// Start the copy of a plan's table image into LDS (dynamic shared memory);
+// all STEP_WAVES waves call it, and stage_wait before the first read.
+// A launch runs only one or two lines per wave, so the tables' latency is
+// part of every step.  Copied through registers in loops (each 4 KiB pass of
+// each table waits for its loads: 11 memory latencies in a row for 8 layers
+// and 1024 rows) the 1024 x 4096 FP64 step took 28.0 us and a 64 x 128 FP32
+// step 5.1 us; with every wave issuing all its pieces of 1 KiB (64 lanes x 16
+// bytes, memory to LDS, no registers) before anything waits, 25.6 and 4.0 us.
+__device__ inline void stage_tables(const unsigned char *img, unsigned char *smem, unsigned bytes) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const unsigned full = bytes >> 10, rem = bytes & 1023;
+    for (unsigned c = wv; c < full; c += STEP_WAVES)
+        __builtin_amdgcn_global_load_lds((const void *)(img + (c << 10) + 16 * lane),
+                                         (__attribute__((address_space(3))) void *)(smem + (c << 10)),
+                                         16, 0, 0);
+    // the last piece, under 1 KiB (a multiple of 16 bytes)
+    if (wv == full % STEP_WAVES && 16u * lane < rem)
+        *(uint4 *)(smem + (full << 10) + 16 * lane) = *(const uint4 *)(img + (full << 10) + 16 * lane);
+}
+// every piece of the tables has landed (vmcnt 0) and every wave knows it
+__device__ inline void stage_wait() {
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    __syncthreads();
+}
+
+// The law evaluators over the staged tables.
 template <typename R>
-__device__ inline LawLds<R> stage_laws(const StepArgs<R> &a, unsigned char *smem) {
-    const int t = threadIdx.x, nt = blockDim.x, L = a.laws.L, nlaw = 3 * L + 2;
+__device__ inline LawLds<R> laws_in(const unsigned char *smem, int L) {
+    const int nlaw = 3 * L + 2;
     LawLds<R> v;
     if constexpr (sizeof(R) == 8) {
-        double *d = (double *)smem;
-        const int nb = (int)pow_blob_doubles(L);
-        for (int i = t; i < nb; i += nt) d[i] = a.pow_blob[i];
-        v.blk = d;
-        v.cka = d + (size_t)nlaw * POW_BLK;
+        v.blk = (const double *)smem;
+        v.cka = v.blk + (size_t)nlaw * POW_BLK;
     } else {
-        float *f = (float *)smem;
-        for (int i = t; i < nlaw; i += nt) {
-            f[i] = (float)a.laws.lk[i];
-            f[nlaw + i] = (float)a.laws.e[i];
-            const bool capl = i >= 2 * L && i < 3 * L;
-            f[2 * nlaw + 2 * i] = capl ? (float)a.laws.K[i] : 0.0f;
-            f[2 * nlaw + 2 * i + 1] = i == law_unit(L) ? 1.0f : 0.0f;
-        }
-        v.lk = f;
-        v.ex = f + nlaw;
-        v.cka = f + 2 * nlaw;
+        v.lk = (const float *)smem;
+        v.ex = v.lk + nlaw;
+        v.cka = v.lk + 2 * nlaw;
     }
-    __syncthreads();
     return v;
 }
-
-// Polynomial laws: the stepping kernel's coefficient blob (POLY_BLK doubles
-// per law id) staged in LDS in the field's type; all threads call it.
-template <typename R>
-__device__ inline LawPoly<R> stage_poly(const StepArgs<R> &a, unsigned char *smem) {
-    const int n = POLY_BLK * (3 * a.laws.L + 2);
-    R *d = (R *)smem;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) d[i] = (R)a.pow_blob[i];
-    __syncthreads();
-    return LawPoly<R>{d};
+template <typename R, bool POLY>
+__device__ inline auto staged_laws(const unsigned char *smem, int L) {
+    if constexpr (POLY) return LawPoly<R>{(const R *)smem};
+    else return laws_in<R>(smem, L);
 }
 
 }  // namespace cryo

@@ -38,12 +38,6 @@ namespace cryo {
 // CUBE: every capacity law has exponent 3 (c(T) by multiplication).
 // POLY: polynomial laws (eqs. (23), (24)), interface rows as the quotient
 // of two laws, and the optional Joule source (eq. (25)).
-template <typename R, bool POLY>
-__device__ inline auto stage_law_of(const StepArgs<R> &a, unsigned char *smem) {
-    if constexpr (POLY) return stage_poly<R>(a, smem);
-    else return stage_laws<R>(a, smem);
-}
-
 // STEPPED: the stepped domain of eq. (9).  Lines above z_full use the
 // terminal's row tables (rows past its wall are identity rows), the axial
 // face between lines z_full and z_full + 1 is closed where the terminal's row
@@ -59,32 +53,22 @@ __device__ inline void step_body(const StepArgs<R> &a, const int blk, const R *_
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double wsum[STEP_WAVES];
     __shared__ R xchg[NG][9 * G];
-    // per-row tables of the line (shared by every line) after the law tables
-    R *sgw = (R *)(smem + ((law_lds_bytes<R>(a.laws.L) + 15) & ~(size_t)15));
-    R *sge = sgw + a.np;
-    uint32_t *sinf = (uint32_t *)(sge + a.np);
-    // STEPPED: the terminal's tables next, where the ring or carried fluxes
-    // would otherwise start (those move up by tbytes)
-    const size_t tbytes = STEPPED ? step_tables_bytes<R>(a.np) : 0;
-    R *sgw2 = (R *)(smem + ring_lds_offset<R>(a.laws.L, a.np));
-    R *sge2 = sgw2 + a.np;
-    uint32_t *sinf2 = (uint32_t *)(sge2 + a.np);
-    for (int i = threadIdx.x; i < a.np; i += blockDim.x) {
-        sgw[i] = a.gw[i];
-        sge[i] = a.ge[i];
-        sinf[i] = a.info[i];
-        if constexpr (STEPPED) {
-            sgw2[i] = a.gw2[i];
-            sge2[i] = a.ge2[i];
-            sinf2[i] = a.info2[i];
-        }
-    }
-    const auto law = stage_law_of<R, POLY>(a, smem);   // ends with a barrier
+    const int L = a.L;
+    const size_t tbytes = tables_bytes<R>(L, a.np, POLY, STEPPED);
+    stage_tables(a.img, smem, (unsigned)tbytes);
+    const auto law = staged_laws<R, POLY>(smem, L);
+    // per-row tables of the line (shared by every line) after the law tables,
+    // the terminal's (STEPPED) after those
+    const R *sgw = (const R *)(smem + law_bytes<R>(L, POLY));
+    const R *sge = sgw + a.np;
+    const uint32_t *sinf = (const uint32_t *)(sge + a.np);
+    const R *sgw2 = (const R *)((const unsigned char *)sgw + (STEPPED ? row_bytes<R>(a.np) : 0));
+    const R *sge2 = sgw2 + a.np;
+    const uint32_t *sinf2 = (const uint32_t *)(sge2 + a.np);
     const int t = threadIdx.x;
     // the wave index is uniform: line indices and bases live in scalar registers
     const int lane = t & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(t / WAVE);
     const int grp = wv / G, wig = wv % G, lg = wig * WAVE + lane;
-    const int L = a.laws.L;
     const int j0 = 1 + (blk * NG + grp) * a.lpw;
     const int j1 = min(j0 + a.lpw, a.nz - 1);             // exclusive
     // Line order: even line groups march up, odd ones down, so that the
@@ -117,7 +101,7 @@ __device__ inline void step_body(const StepArgs<R> &a, const int blk, const R *_
     constexpr bool RING = ring_used<R>(RPL);
     constexpr int EPL = 16 / (int)sizeof(R);              // elements per lane per load
     constexpr int LPS = WAVE / EPL;                       // lanes per row-plane
-    R *ring = (R *)(smem + ring_lds_offset<R>(L, a.np) + tbytes) + (size_t)wv * 2 * SLOT;
+    R *ring = (R *)(smem + tbytes) + (size_t)wv * 2 * SLOT;
     auto prefetch = [&](int slot, size_t lbase) {
         if constexpr (!RING) return;
         R *dst = ring + slot * SLOT;
@@ -135,7 +119,7 @@ __device__ inline void step_body(const StepArgs<R> &a, const int blk, const R *_
     // carried south-face fluxes: registers, or (FP64, 10+ rows per lane) LDS
     constexpr bool FS_LDS = fs_in_lds<R>(RPL);
     R FSr[FS_LDS ? 1 : RPL];
-    R *fsl = (R *)(smem + ring_lds_offset<R>(L, a.np) + tbytes) + (size_t)wv * RPL * WAVE + lane;
+    R *fsl = (R *)(smem + tbytes) + (size_t)wv * RPL * WAVE + lane;
     auto fs_get = [&](int r) -> R {
         if constexpr (FS_LDS) return fsl[r * WAVE];
         else return FSr[r];
@@ -152,6 +136,9 @@ __device__ inline void step_body(const StepArgs<R> &a, const int blk, const R *_
         const size_t bp = (size_t)(jb - dir) * LS;       // the line before it
         const uint32_t *tinf = (STEPPED && jb > a.z_full) ? sinf2 : sinf;
         const bool trans = STEPPED && min(jb, jb - dir) == a.z_full;
+        // (before the lines' loads: waiting for both at once cost 3 to 5 % of
+        // a step, the lines being slower to arrive than the tables)
+        stage_wait();
         prefetch(1, bc + LS);
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
@@ -610,11 +597,9 @@ static StepArgs<R> step_args(const cryo_plan *p, const void *Tin, void *Tout, do
     a.flag = flag;
     a.Tin = (const R *)Tin;
     a.Tout = (R *)Tout;
-    a.gw = (const R *)p->d_rows;
-    a.ge = a.gw + p->np;
-    a.info = p->d_info;
-    a.pow_blob = p->d_pow;
-    a.laws = p->flaws;
+    a.img = p->d_tab;
+    a.L = p->L;
+    a.cube = p->flaws.cube;
     a.nz = p->nz;
     a.np = p->np;
     a.lpw = p->lpw;
@@ -630,12 +615,8 @@ static StepArgs<R> step_args(const cryo_plan *p, const void *Tin, void *Tout, do
     a.wz_end = 0.5 / (p->nz - 1);
     a.surf_lane = p->surf_lane;
     a.surf_reg = p->surf_reg;
-    // stepped domain: the terminal's tables, and the surface over lines
-    // 0..z_full
+    // stepped domain: the surface over lines 0..z_full
     a.z_full = p->stepped ? p->z_full : p->nz - 1;
-    a.gw2 = p->stepped ? (const R *)p->d_rows2 : a.gw;
-    a.ge2 = p->stepped ? a.gw2 + p->np : a.ge;
-    a.info2 = p->stepped ? p->d_info2 : a.info;
     if (p->stepped) {
         a.wz_mid = 1.0 / p->z_full;
         a.wz_end = 0.5 / p->z_full;
@@ -662,7 +643,7 @@ static cryo_status step_t(const cryo_plan *p, const void *Tin, void *Tout, doubl
             break; \
         } \
         if (p->stepped) { \
-            if (a.laws.cube) hipLaunchKernelGGL((k_step<R, RP, GW, true, false, true>), g, b, lds, s, a); \
+            if (a.cube) hipLaunchKernelGGL((k_step<R, RP, GW, true, false, true>), g, b, lds, s, a); \
             else hipLaunchKernelGGL((k_step<R, RP, GW, false, false, true>), g, b, lds, s, a); \
             break; \
         } \
@@ -670,7 +651,7 @@ static cryo_status step_t(const cryo_plan *p, const void *Tin, void *Tout, doubl
             hipLaunchKernelGGL((k_step<R, RP, GW, false, true>), g, b, lds, s, a); \
             break; \
         } \
-        if (a.laws.cube) hipLaunchKernelGGL((k_step<R, RP, GW, true>), g, b, lds, s, a); \
+        if (a.cube) hipLaunchKernelGGL((k_step<R, RP, GW, true>), g, b, lds, s, a); \
         else hipLaunchKernelGGL((k_step<R, RP, GW, false>), g, b, lds, s, a); \
         break;
         CRYO_FOR_SHAPES(STEP_CASE)
@@ -702,13 +683,56 @@ size_t step_desc_bytes(cryo_dtype dt) {
     return dt == CRYO_F64 ? sizeof(StepArgs<double>) : sizeof(StepArgs<float>);
 }
 
+template <typename R>
+static size_t step_lds_t(const cryo_plan *p, bool reserve) {
+    // (a reserve holds power tables, or for FP32 POLY_BLK floats per law)
+    const size_t tab = tables_bytes<R>(p->L, p->np, reserve ? sizeof(R) == 4 : p->poly, p->stepped);
+    return tab + line_lds_bytes<R>(p->rpl);
+}
 size_t step_lds(const cryo_plan *p) {
-    // a stepped domain stages the terminal's tables too
-    return p->dtype == CRYO_F64
-               ? step_lds_bytes<double>(p->L, p->np, p->rpl) +
-                     (p->stepped ? step_tables_bytes<double>(p->np) : 0)
-               : step_lds_bytes<float>(p->L, p->np, p->rpl) +
-                     (p->stepped ? step_tables_bytes<float>(p->np) : 0);
+    return p->dtype == CRYO_F64 ? step_lds_t<double>(p, false) : step_lds_t<float>(p, false);
+}
+size_t step_lds_reserve(const cryo_plan *p) {
+    return p->dtype == CRYO_F64 ? step_lds_t<double>(p, true) : step_lds_t<float>(p, true);
+}
+
+// The image of tables_bytes: what ensure_device uploads once.
+template <typename R>
+static std::vector<unsigned char> table_image_t(const cryo_plan *p) {
+    std::vector<unsigned char> img(tables_bytes<R>(p->L, p->np, p->poly, p->stepped), 0);
+    const int nlaw = 3 * p->L + 2;
+    R *law = (R *)img.data();
+    if (p->poly) {
+        for (int i = 0; i < POLY_BLK * nlaw; ++i) law[i] = (R)p->fpow_blob[i];
+    } else if constexpr (sizeof(R) == 8) {
+        memcpy(law, p->fpow_blob.data(), sizeof(double) * pow_blob_doubles(p->L));
+    } else {
+        const Laws &l = p->flaws;
+        for (int i = 0; i < nlaw; ++i) {
+            law[i] = (R)l.lk[i];
+            law[nlaw + i] = (R)l.e[i];
+            const bool capl = i >= 2 * p->L && i < 3 * p->L;
+            law[2 * nlaw + 2 * i] = capl ? (R)l.K[i] : (R)0;
+            law[2 * nlaw + 2 * i + 1] = i == law_unit(p->L) ? (R)1 : (R)0;
+        }
+    }
+    unsigned char *rows = img.data() + law_bytes<R>(p->L, p->poly);
+    auto put = [&](const std::vector<double> &gw, const std::vector<double> &ge,
+                   const std::vector<uint32_t> &info) {
+        R *g = (R *)rows;
+        for (int i = 0; i < p->np; ++i) {
+            g[i] = (R)gw[i];
+            g[p->np + i] = (R)ge[i];
+        }
+        memcpy(g + 2 * (size_t)p->np, info.data(), sizeof(uint32_t) * p->np);
+        rows += row_bytes<R>(p->np);
+    };
+    put(p->fgw, p->fge, p->finfo);
+    if (p->stepped) put(p->tfgw, p->tfge, p->tfinfo);
+    return img;
+}
+std::vector<unsigned char> table_image(const cryo_plan *p) {
+    return p->dtype == CRYO_F64 ? table_image_t<double>(p) : table_image_t<float>(p);
 }
 
 void step_desc_fill(const cryo_plan *p, void *out, void *buf0, void *buf1, int *flag) {

@@ -22,7 +22,7 @@ cryo_status launch_adj_init(const cryo_plan *p, double *lam, const double *cS, h
 cryo_status launch_zero(double *ptr, size_t n, hipStream_t s);
 int adj_slots(const cryo_plan *p);
 int adj_grid(const cryo_plan *p);
-size_t adj_lds(const cryo_plan *p);
+size_t adj_lds_reserve(const cryo_plan *p);
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -321,7 +321,7 @@ static cryo_status grad_check(const cryo_plan *p, int64_t N, const double *targe
                               const void *T0, void *ws, size_t ws_bytes) {
     if (!p || !T0 || N < 1 || !target || ckpt < 0) return fail(CRYO_ERR_ARG, "bad argument");
     if (p->dtype != CRYO_F64) return fail(CRYO_ERR_UNSUPPORTED, "the adjoint needs an FP64 plan");
-    if (adj_lds(p) > MAX_STEP_LDS)
+    if (adj_lds_reserve(p) > MAX_STEP_LDS)
         return fail(CRYO_ERR_UNSUPPORTED, "the adjoint's tables exceed a workgroup's LDS for this "
                                           "shape; choose fewer rows per line");
     const int key = p->rpl * 10 + p->wpl;

@@ -208,48 +208,12 @@ static int pick_lpw(int nz, int wpl) {
 // Device copies of the per-row tables, made once on the first call that
 // needs the device (on the device current at that time).
 cryo_status ensure_device(cryo_plan *p) {
-    if (p->d_info) return CRYO_OK;
+    if (p->d_tab) return CRYO_OK;
     (void)hipGetDevice(&p->device);
-    const int np = p->np;
-    size_t es = p->dtype == CRYO_F64 ? sizeof(double) : sizeof(float);
-    // one array of two planes: fgw, fge
-    std::vector<double> rows(p->fgw);
-    rows.insert(rows.end(), p->fge.begin(), p->fge.end());
-    const std::vector<double> &blobs = p->fpow_blob;
-    hipError_t e = hipMalloc(&p->d_rows, es * 2 * np);
-    uint32_t *info = nullptr;
-    if (e == hipSuccess) e = hipMalloc((void **)&info, sizeof(uint32_t) * np);
-    if (e == hipSuccess) {
-        if (p->dtype == CRYO_F64) {
-            e = hipMemcpy(p->d_rows, rows.data(), es * 2 * np, hipMemcpyHostToDevice);
-        } else {
-            std::vector<float> a(rows.begin(), rows.end());
-            e = hipMemcpy(p->d_rows, a.data(), es * 2 * np, hipMemcpyHostToDevice);
-        }
-    }
-    if (e == hipSuccess)
-        e = hipMemcpy(info, p->finfo.data(), sizeof(uint32_t) * np, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void **)&p->d_pow, sizeof(double) * blobs.size());
-    if (e == hipSuccess)
-        e = hipMemcpy(p->d_pow, blobs.data(), sizeof(double) * blobs.size(),
-                      hipMemcpyHostToDevice);
-    if (e == hipSuccess && p->stepped) {
-        std::vector<double> t(p->tfgw);
-        t.insert(t.end(), p->tfge.begin(), p->tfge.end());
-        e = hipMalloc(&p->d_rows2, es * 2 * np);
-        if (e == hipSuccess) {
-            if (p->dtype == CRYO_F64) {
-                e = hipMemcpy(p->d_rows2, t.data(), es * 2 * np, hipMemcpyHostToDevice);
-            } else {
-                std::vector<float> f(t.begin(), t.end());
-                e = hipMemcpy(p->d_rows2, f.data(), es * 2 * np, hipMemcpyHostToDevice);
-            }
-        }
-        if (e == hipSuccess) e = hipMalloc((void **)&p->d_info2, sizeof(uint32_t) * np);
-        if (e == hipSuccess)
-            e = hipMemcpy(p->d_info2, p->tfinfo.data(), sizeof(uint32_t) * np,
-                          hipMemcpyHostToDevice);
-    }
+    const std::vector<unsigned char> img = table_image(p);
+    unsigned char *tab = nullptr;
+    hipError_t e = hipMalloc((void **)&tab, img.size());
+    if (e == hipSuccess) e = hipMemcpy(tab, img.data(), img.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && p->dtype == CRYO_F64) {
         const std::vector<double> gt = grad_param_table(p);
         e = hipMalloc((void **)&p->d_grad, sizeof(double) * gt.size());
@@ -257,20 +221,12 @@ cryo_status ensure_device(cryo_plan *p) {
             e = hipMemcpy(p->d_grad, gt.data(), sizeof(double) * gt.size(), hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
-        if (p->d_rows) (void)hipFree(p->d_rows);
-        if (info) (void)hipFree(info);
-        if (p->d_pow) (void)hipFree(p->d_pow);
-        if (p->d_rows2) (void)hipFree(p->d_rows2);
-        if (p->d_info2) (void)hipFree(p->d_info2);
+        if (tab) (void)hipFree(tab);
         if (p->d_grad) (void)hipFree(p->d_grad);
-        p->d_rows = nullptr;
-        p->d_pow = nullptr;
-        p->d_rows2 = nullptr;
-        p->d_info2 = nullptr;
         p->d_grad = nullptr;
         return fail(CRYO_ERR_DEVICE, std::string("device table upload: ") + hipGetErrorString(e));
     }
-    p->d_info = info;
+    p->d_tab = tab;
     return CRYO_OK;
 }
 
@@ -482,7 +438,7 @@ cryo_status cryo_plan_create(const cryo_problem *prob, cryo_dtype dtype, cryo_pl
         fl.lk[id] = fl.K[id] > 0 ? log2(fl.K[id]) - fl.e[id] : -2000.0;
     fill_pow_blob(fl, p->fpow_blob);
 
-    if (step_lds(p) > MAX_STEP_LDS) {
+    if (step_lds_reserve(p) > MAX_STEP_LDS) {
         delete p;
         return fail(CRYO_ERR_UNSUPPORTED, "tables and line ring exceed a workgroup's LDS");
     }
@@ -499,11 +455,7 @@ cryo_status cryo_plan_create(const cryo_problem *prob, cryo_dtype dtype, cryo_pl
 void cryo_plan_destroy(cryo_plan *p) {
     if (!p) return;
     cryo_plan_destroy(p->sub);
-    if (p->d_rows) (void)hipFree(p->d_rows);
-    if (p->d_info) (void)hipFree(p->d_info);
-    if (p->d_pow) (void)hipFree(p->d_pow);
-    if (p->d_rows2) (void)hipFree(p->d_rows2);
-    if (p->d_info2) (void)hipFree(p->d_info2);
+    if (p->d_tab) (void)hipFree(p->d_tab);
     if (p->d_grad) (void)hipFree(p->d_grad);
     delete p;
 }
@@ -520,7 +472,7 @@ cryo_status cryo_plan_shape(const cryo_plan *p, int32_t *rows_per_lane,
 cryo_status cryo_plan_set_shape(cryo_plan *p, int32_t rows_per_lane, int32_t waves_per_line,
                                 int32_t lines_per_wave) {
     if (!p) return fail(CRYO_ERR_ARG, "null plan");
-    if (p->d_info) return fail(CRYO_ERR_ARG, "shape must be set before the plan's first run");
+    if (p->d_tab) return fail(CRYO_ERR_ARG, "shape must be set before the plan's first run");
     if (!shape_built(rows_per_lane, waves_per_line))
         return fail(CRYO_ERR_UNSUPPORTED, "no kernel for this chunk shape");
     if ((int64_t)WAVE * waves_per_line * rows_per_lane < p->nr)
@@ -533,7 +485,7 @@ cryo_status cryo_plan_set_shape(cryo_plan *p, int32_t rows_per_lane, int32_t wav
         p->rpl = rows_per_lane;
         p->wpl = waves_per_line;
         p->np = WAVE * p->wpl * p->rpl;
-        if (step_lds(p) > MAX_STEP_LDS) {
+        if (step_lds_reserve(p) > MAX_STEP_LDS) {
             p->rpl = rpl0;
             p->wpl = wpl0;
             p->np = WAVE * p->wpl * p->rpl;
@@ -555,7 +507,7 @@ static double poly_at(const double *c, int n, double T) {
 cryo_status cryo_plan_set_poly_laws(cryo_plan *p, const double *a, const double *b,
                                     double joule_tref) {
     if (!p || !a || !b) return fail(CRYO_ERR_ARG, "null argument");
-    if (p->d_info) return fail(CRYO_ERR_ARG, "laws must be set before the plan's first run");
+    if (p->d_tab) return fail(CRYO_ERR_ARG, "laws must be set before the plan's first run");
     const int L = p->L;
     for (int i = 0; i < 4 * L; ++i)
         if (!std::isfinite(a[i])) return fail(CRYO_ERR_ARG, "capacity coefficient not finite");
@@ -613,13 +565,13 @@ cryo_status cryo_plan_set_poly_laws(cryo_plan *p, const double *a, const double 
 
 cryo_status cryo_plan_set_stepped(cryo_plan *p, int32_t z_full, int32_t nr_top) {
     if (!p) return fail(CRYO_ERR_ARG, "null plan");
-    if (p->d_info) return fail(CRYO_ERR_ARG, "the domain must be set before the plan's first run");
+    if (p->d_tab) return fail(CRYO_ERR_ARG, "the domain must be set before the plan's first run");
     if (z_full < 1 || z_full > p->nz - 2) return fail(CRYO_ERR_ARG, "z_full must be 1..nz-2");
     if (nr_top < 3 || nr_top > p->nr) return fail(CRYO_ERR_ARG, "nr_top must be 3..nr");
     p->stepped = true;
     p->z_full = z_full;
     p->nr_top = nr_top;
-    if (step_lds(p) > MAX_STEP_LDS) {
+    if (step_lds_reserve(p) > MAX_STEP_LDS) {
         p->stepped = false;
         return fail(CRYO_ERR_UNSUPPORTED, "the terminal's tables exceed a workgroup's LDS");
     }
@@ -767,7 +719,7 @@ cryo_status forward_in(const cryo_plan *p, void *T, int64_t k0, int64_t nsteps, 
 }
 
 bool plan_tables_on_device(const cryo_plan *p) {
-    return p->d_info != nullptr && (!p->sub || p->sub->d_info != nullptr);
+    return p->d_tab != nullptr && (!p->sub || p->sub->d_tab != nullptr);
 }
 }  // namespace cryo
 

@@ -160,9 +160,7 @@ struct cryo_plan {
     cryo::Pulse pulse;
     int surf_lane, surf_reg;          // owner of row nr-1
     // device tables (read-only, made at create time)
-    void *d_rows = nullptr;           // [2][np]: fgw, fge
-    uint32_t *d_info = nullptr;       // [np]: finfo
-    double *d_pow = nullptr;          // fpow_blob
+    unsigned char *d_tab = nullptr;   // the kernels' table image (see tables_bytes)
     int device = 0;
     // transient turn-on model (eq. (22)): the same cell at dt / 100, whose
     // tables step the sub-steps of each pulse-start step (null when off)
@@ -180,8 +178,6 @@ struct cryo_plan {
     int z_full = 0, nr_top = 0;
     std::vector<double> tfgw, tfge;
     std::vector<uint32_t> tfinfo;
-    void *d_rows2 = nullptr;          // [2][np]: tfgw, tfge
-    uint32_t *d_info2 = nullptr;      // [np]: tfinfo
     // FP64 plans: the parameter weights of the gradient (grad_param_table)
     double *d_grad = nullptr;
     // kernel steps at the end of a gradient's run whose states its forward
@@ -209,6 +205,10 @@ cryo_status launch_surf_reduce(const cryo_plan *p, const double *partial, int ns
                                double *out, hipStream_t s);
 int step_grid(const cryo_plan *p);
 size_t step_lds(const cryo_plan *p);            // dynamic LDS of the stepping kernel
+// what a plan is accepted against: the LDS its shape and domain would take
+// with power tables of either kind (laws may be replaced after the check)
+size_t step_lds_reserve(const cryo_plan *p);
+std::vector<unsigned char> table_image(const cryo_plan *p);
 constexpr size_t MAX_STEP_LDS = 160 * 1024 - 4096;   // leaves room for static LDS
 cryo_status ensure_device(cryo_plan *p);
 // host.hip: cryo_forward's device work on a checked workspace, and whether
