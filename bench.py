@@ -44,8 +44,8 @@ GRAD_STORE_GIB = 200              # device memory the stored-tail gradient may t
 # counter summary, and only when that summary was taken on the kernel
 # sources of this tree (their hash is written in it); otherwise null.
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_step_f64_1024x4096.md")
-KERNEL_SOURCES = ["paper_1408_5853_amd/csrc/forward.hip", "paper_1408_5853_amd/csrc/device_common.h",
-                  "paper_1408_5853_amd/csrc/internal.h"]
+KERNEL_SOURCES = ["paper_1408_5853_amd/csrc/step_kernel.h", "paper_1408_5853_amd/csrc/forward.hip",
+                  "paper_1408_5853_amd/csrc/device_common.h", "paper_1408_5853_amd/csrc/internal.h"]
 
 
 def log(*a):

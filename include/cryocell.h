@@ -155,9 +155,8 @@ void cryo_plan_destroy(cryo_plan *plan);
  * Built shapes: one wave per line with 2, 3, 4, 5, 6, 7, 8, 10, 12 or 16
  * rows per lane, and (4,2) (8,2) (4,4) (8,4); 64 * waves * rows must cover
  * nr.  The gradient runs (2,1) (4,1) (8,1) (4,2) (8,2) (4,4) (8,4).  Other
- * shapes, lines per wave included, change only rounding: the chunks of the
- * line solve, and the order in which a line adds its two axial fluxes (its
- * line block's march direction), depend on the shape. */
+ * shapes change only rounding (the chunks of the line solve depend on the
+ * shape; lines per wave only regroup the surface mean's partial sums). */
 cryo_status cryo_plan_shape(const cryo_plan *plan, int32_t *rows_per_lane,
                             int32_t *waves_per_line, int32_t *lines_per_wave);
 cryo_status cryo_plan_set_shape(cryo_plan *plan, int32_t rows_per_lane,

@@ -34,6 +34,11 @@ namespace cryo {
 
 constexpr int ADJ_WAVES = 8;
 
+// Couplings that the transposed line solves leave out (solve_tail), far below
+// what any sum of a gradient keeps: an adjoint state falls off by orders of
+// magnitude away from the observed surface.
+constexpr double ADJ_DROP = 0x1p-200;
+
 // pass 1 keeps per-row sums in LDS after the tables
 __host__ __device__ inline size_t adj_lds_bytes(int L, int np, int rpl, bool poly, bool stepped) {
     return tables_bytes<double>(L, np, poly, stepped) +
@@ -74,14 +79,14 @@ struct AdjLds {
 template <bool STEPPED, bool POLY = false>
 __device__ inline AdjLds<POLY> adj_stage(const StepArgs<double> &a, unsigned char *smem) {
     const size_t tbytes = tables_bytes<double>(a.L, a.np, POLY, STEPPED);
-    stage_tables(a.img, smem, (unsigned)tbytes);
+    stage_tables(a.img, (unsigned)tbytes, nullptr, 0, smem);
     AdjLds<POLY> t;
     t.sgw = (const double *)(smem + law_bytes<double>(a.L, POLY));
     t.sge = t.sgw + a.np;
-    t.sinf = (const uint32_t *)(t.sge + a.np);
-    t.sgw2 = (const double *)((const unsigned char *)t.sgw + (STEPPED ? row_bytes<double>(a.np) : 0));
+    t.sgw2 = t.sgw + (STEPPED ? 2 * a.np : 0);
     t.sge2 = t.sgw2 + a.np;
-    t.sinf2 = (const uint32_t *)(t.sge2 + a.np);
+    t.sinf = (const uint32_t *)(smem + info_offset<double>(a.L, a.np, POLY, STEPPED));
+    t.sinf2 = t.sinf + (STEPPED ? a.np : 0);
     t.sums = (double *)(smem + tbytes);
     t.law = staged_laws<double, POLY>(smem, a.L);
     stage_wait();
@@ -231,7 +236,7 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
         }
         elim_row<double, RPL>(RPL - 1, ccm2, bbm1, aaNext, mum1, al, ga, de);
         double y[RPL];
-        solve_tail<double, RPL, G>(a0, b0, c0, d0, al, ga, de, y, lane, wig, xchg[grp]);
+        solve_tail<double, RPL, G>(a0, b0, c0, d0, al, ga, de, y, lane, wig, xchg[grp], ADJ_DROP);
         // T^{n+1} of the line, loaded after the solve (registers)
         double X[RPL];
 #pragma unroll
@@ -315,7 +320,7 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
                     drc = poly_dlaw(law, lc, t);
                 } else if constexpr (CUBE) {
                     rc = law.cube(lc, t);
-                    drc = 3.0 * law.cka[2 * lc] * t * t;
+                    drc = 3.0 * law.cubek(lc) * t * t;
                 } else {
                     rc = law.lawc(lc, t);
                     drc = law.expo(lc) * rc * rcp(t);
@@ -581,7 +586,7 @@ size_t adj_lds(const cryo_plan *p) {
     return adj_lds_bytes(p->L, p->np, p->rpl, p->poly, p->stepped);
 }
 size_t adj_lds_reserve(const cryo_plan *p) {
-    return adj_lds_bytes(p->L, p->np, p->rpl, false, p->stepped);
+    return tables_reserve(p) + 2 * (size_t)ADJ_WAVES * p->rpl * WAVE * sizeof(double);
 }
 
 StepArgs<double> step_args_f64(const cryo_plan *p, int *flag);

@@ -23,6 +23,7 @@ struct Bucket {
     bool cube;                       // every capacity exponent is 3
     bool poly;                       // polynomial laws (eqs. (23)-(25))
     bool stepped;                    // stepped domain (eq. (9))
+    bool shared;                     // one line per wave (step_shared)
     std::vector<int> inst;           // instance indices
     std::vector<int2> map;           // workgroup -> (instance, workgroup of instance)
     size_t desc_off = 0, map_off = 0;  // byte offsets in the device block
@@ -61,8 +62,8 @@ static int64_t abi_elems(const cryo_plan *p) {
 size_t step_desc_bytes(cryo_dtype dt);
 void step_desc_fill(const cryo_plan *p, void *out, void *buf0, void *buf1, int *flag);
 cryo_status launch_step_batch(cryo_dtype dt, int rpl, int wpl, bool cube, bool poly,
-                              bool stepped, const void *desc, const int2 *map, int nwg,
-                              size_t lds, int64_t n, const int64_t *k0, hipStream_t s);
+                              bool stepped, bool shared, const void *desc, const int2 *map,
+                              int nwg, size_t lds, int64_t n, const int64_t *k0, hipStream_t s);
 cryo_status launch_set_i64(int64_t *ptr, int64_t v, hipStream_t s);
 cryo_status launch_add_i64(int64_t *ptr, int64_t v, hipStream_t s);
 
@@ -93,10 +94,11 @@ static cryo_status batch_build_buckets(cryo_batch *b) {
     std::map<int, int> idx;
     for (size_t i = 0; i < b->plans.size(); ++i) {
         const cryo_plan *p = b->plans[i];
-        // shape, law family (cube, power, polynomial) and domain
+        // shape, law family (cube, power, polynomial), domain, and whether
+        // each wave takes one line
         const bool cube = !p->poly && p->flaws.cube != 0;
         int key = p->rpl * 10 + p->wpl + (cube ? 1000 : 0) + (p->poly ? 2000 : 0) +
-                  (p->stepped ? 4000 : 0);
+                  (p->stepped ? 4000 : 0) + (step_shared(p) ? 8000 : 0);
         if (!idx.count(key)) {
             idx[key] = (int)b->buckets.size();
             Bucket bk;
@@ -105,6 +107,7 @@ static cryo_status batch_build_buckets(cryo_batch *b) {
             bk.cube = cube;
             bk.poly = p->poly;
             bk.stepped = p->stepped;
+            bk.shared = step_shared(p);
             b->buckets.push_back(bk);
         }
         Bucket &bk = b->buckets[idx[key]];
@@ -276,7 +279,7 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
         for (int i : bk.inst) lds = std::max(lds, step_lds(b->plans[i]));
         for (int64_t m = first; m < first + count; ++m) {
             cryo_status r = launch_step_batch(
-                b->dtype, bk.rpl, bk.wpl, bk.cube, bk.poly, bk.stepped,
+                b->dtype, bk.rpl, bk.wpl, bk.cube, bk.poly, bk.stepped, bk.shared,
                 (const char *)b->d_block + bk.desc_off,
                 (const int2 *)((const char *)b->d_block + bk.map_off), (int)bk.map.size(), lds,
                 m, k0p, strm);

@@ -6,6 +6,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace cryo {
@@ -24,108 +26,160 @@ __device__ inline float rcp(float x) {
     return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
 
-// Law evaluation K[id] * T^e[id] from tables staged in LDS.
+// Law evaluation K[id] * T^e[id] from tables staged in LDS.  A Set holds one
+// radial law's constants in a lane's registers, `at` evaluates it at the mean
+// of two values given their sum, `next` moves on to the next layer's, `ratio`
+// is the quotient of this layer's law and the next one's at s / 2, and `cap`
+// the layer's capacity law at T (CUBE: every exponent is 3).
 template <typename R>
 struct LawLds;
 
 template <>
 struct LawLds<double> {
     const double *blk;      // law blocks (POW_BLK doubles per law id)
-    const double *cka;      // cube path: K T^3 + A, pairs {K, A} per law id
-    // T on the table range [2^POW_EMIN, 2^(POW_EMIN+POW_NE)) K
-    static __device__ inline bool in_range(double x) {
-        return x >= POW_TLO && x < POW_THI;
+    int L;
+    struct Set {
+        const double *B;
+        double e, k;         // exponent; the layer's cube multiplier
+        double2 c23, c45, c67;
+    };
+    static __device__ inline Set load(const double *B) {
+        Set s;
+        s.B = B;
+        const double2 ek = *(const double2 *)(B + POW_BE);
+        s.e = ek.x;
+        s.k = ek.y;
+        s.c23 = *(const double2 *)(B + POW_BE + 2);
+        s.c45 = *(const double2 *)(B + POW_BE + 4);
+        s.c67 = *(const double2 *)(B + POW_BE + 6);
+        return s;
     }
+    __device__ inline Set set(int id) const { return load(blk + id * POW_BLK); }
+    __device__ inline void next(Set &s) const { s = load(s.B + POW_BLK); }
+    // T on the table range [2^POW_EMIN, 2^(POW_EMIN+POW_NE)) K: the high
+    // words' distance from the lower end, as an unsigned number (NaN and
+    // negative values are far above)
+    static __device__ inline unsigned off_range(double x) {
+        return (unsigned)(__double_as_longlong(x) >> 32) - POW_HLO;
+    }
+    static __device__ inline bool in_range(double x) { return off_range(x) < POW_HN; }
     __device__ inline double expo(int id) const { return blk[id * POW_BLK + POW_BE]; }
-    // K[id] T^e[id]; T off the table range (or not finite) is clamped to its
-    // edge binade, so callers check the range themselves (in_range)
-    __device__ inline double lawc(int id, double x) const { return pw<1>(id, x); }
-    // K[id] (s/2)^e[id]: the law at the mean of two values given their sum s
-    // (halving only moves the binade: same tables, index one binade lower)
-    __device__ inline double lawm(int id, double s) const { return pw<2>(id, s); }
+    // the law at x, and at s / 2 (halving only moves the binade); an argument
+    // off the table range reads some binade's slot, so callers check the
+    // range themselves
+    __device__ inline double lawc(int id, double x) const { return pw<1>(set(id), x); }
+    __device__ inline double lawm(int id, double s) const { return pw<2>(set(id), s); }
+    static __device__ inline double at(const Set &c, double s) { return pw<2>(c, s); }
     template <int SH>
-    __device__ inline double pw(int id, double x) const {
+    static __device__ inline double pw(const Set &c, double x) {
+#pragma clang fp contract(off)                    // (a value does not depend on its use)
         const double mh = __builtin_amdgcn_frexp_mant(x);          // x = mh 2^xe, mh in [1/2, 1)
-        const int xe = __builtin_amdgcn_frexp_exp(x);
-        const int xc = min(max(xe, POW_EMIN + SH), POW_EMIN + POW_NE + SH - 1) - (POW_EMIN + SH);
         const unsigned hi = (unsigned)(__double_as_longlong(x) >> 32);
-        const int jm = (int)__builtin_amdgcn_ubfe(hi, 20 - POW_MBITS, POW_MBITS);
-        const double *B = blk + id * POW_BLK;
-        const double2 ee = *(const double2 *)(B + POW_BE);      // e
-        const double2 c23 = *(const double2 *)(B + POW_BE + 2);
-        const double2 c45 = *(const double2 *)(B + POW_BE + 4);
-        const double2 c67 = *(const double2 *)(B + POW_BE + 6);
-        const double2 mm = *(const double2 *)(B + 2 * jm);
+        const unsigned jm = __builtin_amdgcn_ubfe(hi, 20 - POW_MBITS, POW_MBITS);
+        // the argument's binade is its biased exponent less 1023, the mean's
+        // one lower; 1024 is 0 mod NX
+        const unsigned xc = SH == 2 ? __builtin_amdgcn_ubfe(hi, 20, 5)
+                                    : ((hi >> 20) + 1) & (POW_NX - 1);
+        const double2 mm = *(const double2 *)(c.B + 2 * jm);
         const double u = fma(mh, mm.y, -1.0);                   // m / m0 - 1
         // (1 + u)^e, |u| <= 2^-(POW_MBITS+1), by Estrin's scheme (depth 4,
         // against 7 dependent steps for Horner's)
         const double u2 = u * u, u4 = u2 * u2;
-        const double p01 = fma(ee.x, u, 1.0), p23 = fma(c23.y, u, c23.x);
-        const double p45 = fma(c45.y, u, c45.x), p67 = fma(c67.y, u, c67.x);
+        const double p01 = fma(c.e, u, 1.0), p23 = fma(c.c23.y, u, c.c23.x);
+        const double p45 = fma(c.c45.y, u, c.c45.x), p67 = fma(c.c67.y, u, c.c67.x);
         const double s = fma(fma(p67, u2, p45), u4, fma(p23, u2, p01));
-        return (B[POW_BX + xc] * mm.x) * s;
+        return (c.B[POW_BX + xc] * mm.x) * s;
     }
-    // as lawc, and flags an argument off the table range
-    __device__ inline double law(int id, double x, int &bad) const {
-        bad |= !in_range(x);
-        return lawc(id, x);
+    __device__ inline double ratio(const Set &s, double x) const {
+        return at(load(s.B + L * POW_BLK), x);
     }
+    template <bool CUBE>
+    __device__ inline double cap(const Set &s, double T) const {
+#pragma clang fp contract(off)
+        if constexpr (CUBE) return s.k * (T * T * T);
+        else return at(load(s.B + 2 * L * POW_BLK), T + T);
+    }
+    // capacity of a row by its capacity law's id (K T^3 + A): a layer's, or the
+    // zero and unit laws of other rows
     __device__ inline double cube(int id, double x) const {
-        const double2 k = *(const double2 *)(cka + 2 * id);
+        const double2 k = *(const double2 *)(blk + (3 * L + 2) * POW_BLK + 2 * id);
         return fma(k.x, x * x * x, k.y);
     }
+    __device__ inline double cubek(int id) const { return blk[(3 * L + 2) * POW_BLK + 2 * id]; }
 };
 
 // Polynomial laws (eqs. (23), (24)): sum_k c_k x^k, k <= 4, by Horner's
-// rule, from POLY_BLK doubles per law id staged in LDS in place of the power
-// tables (c_0 .. c_4, one pad).  Interface rows need a quotient of two laws,
-// which callers form.
+// rule, from POLY_BLK numbers per law id staged in LDS in place of the power
+// tables (c_0 .. c_4, one pad); FP32 holds the coefficients rounded to float.
 template <typename R>
-struct LawPoly;
-template <>
-struct LawPoly<double> {
-    const double *c;
-    static __device__ inline bool in_range(double x) { return LawLds<double>::in_range(x); }
-    __device__ inline double lawc(int id, double x) const {
-        const double2 k01 = *(const double2 *)(c + POLY_BLK * id);
-        const double2 k23 = *(const double2 *)(c + POLY_BLK * id + 2);
-        const double k4 = c[POLY_BLK * id + 4];
-        return fma(fma(fma(fma(k4, x, k23.y), x, k23.x), x, k01.y), x, k01.x);
+struct LawPoly {
+    using R2 = std::conditional_t<sizeof(R) == 8, double2, float2>;
+    const R *c;
+    int L;
+    struct Set {
+        const R *B;
+        R2 k01, k23;
+        R k4;
+    };
+    static __device__ inline Set load(const R *p) {
+        return Set{p, *(const R2 *)p, *(const R2 *)(p + 2), p[4]};
     }
-    // the law at the mean of two values given their sum
-    __device__ inline double lawm(int id, double s) const { return lawc(id, 0.5 * s); }
-};
-// FP32 pairs: the same coefficients rounded to float, Horner's rule in float
-template <>
-struct LawPoly<float> {
-    const float *c;
-    __device__ inline float lawc(int id, float x) const {
-        const float2 k01 = *(const float2 *)(c + POLY_BLK * id);
-        const float2 k23 = *(const float2 *)(c + POLY_BLK * id + 2);
-        const float k4 = c[POLY_BLK * id + 4];
-        return fmaf(fmaf(fmaf(fmaf(k4, x, k23.y), x, k23.x), x, k01.y), x, k01.x);
+    __device__ inline Set set(int id) const { return load(c + POLY_BLK * id); }
+    __device__ inline void next(Set &s) const { s = load(s.B + POLY_BLK); }
+    static __device__ inline unsigned off_range(R x) { return LawLds<double>::off_range(x); }
+    static __device__ inline bool in_range(R x) { return LawLds<double>::in_range(x); }
+    static __device__ inline R horner(const Set &s, R x) {
+        return fma(fma(fma(fma(s.k4, x, s.k23.y), x, s.k23.x), x, s.k01.y), x, s.k01.x);
     }
-    __device__ inline float lawm(int id, float s) const { return lawc(id, 0.5f * s); }
+    __device__ inline R lawc(int id, R x) const { return horner(set(id), x); }
+    __device__ inline R lawm(int id, R s) const { return lawc(id, (R)0.5 * s); }
+    static __device__ inline R at(const Set &c, R s) { return horner(c, (R)0.5 * s); }
+    __device__ inline R ratio(const Set &s, R x) const {
+        return at(s, x) / at(load(s.B + POLY_BLK), x);
+    }
+    template <bool CUBE>
+    __device__ inline R cap(const Set &s, R T) const {
+        return horner(load(s.B + 2 * L * POLY_BLK), T);
+    }
 };
 
 // FP32: 2^(e log2 s + lk); the stepping kernel's tables hold lk = log2 K - e,
-// so that s is the sum of the two values whose mean the law is taken at.
+// so that s is the sum of the two values whose mean the law is taken at, with
+// e and the layer's cube multiplier, one float4 per law.
 // The hardware log2 and exp2 instructions serve directly: s is a sum of two
-// temperatures (a normal float), and the zero law's exponent (lk = -2000)
-// gives 0; only law values below 1e-38, which no law here reaches, could
-// differ from the library functions, which add a rescaling for subnormal
-// arguments and results around the same instructions (six more instructions
-// per law).
+// temperatures (a normal float); only law values below 1e-38, which no law
+// here reaches, could differ from the library functions, which add a
+// rescaling for subnormal arguments and results around the same instructions
+// (six more instructions per law).
 template <>
 struct LawLds<float> {
-    const float *lk, *ex, *cka;
-    static __device__ inline bool in_range(float) { return true; }
-    __device__ inline float lawm(int id, float s) const {
-        return __builtin_amdgcn_exp2f(fmaf(ex[id], __builtin_amdgcn_logf(s), lk[id]));
+    const float4 *t;
+    int L;
+    struct Set {
+        const float4 *B;
+        float lk, e, k;
+    };
+    static __device__ inline Set load(const float4 *B) {
+        const float4 v = *B;
+        return Set{B, v.x, v.y, v.z};
     }
+    __device__ inline Set set(int id) const { return load(t + id); }
+    __device__ inline void next(Set &s) const { s = load(s.B + 1); }
+    static __device__ inline unsigned off_range(float) { return 0; }
+    __device__ inline float lawm(int id, float s) const { return at(set(id), s); }
     __device__ inline float cube(int id, float x) const {
-        const float2 k = *(const float2 *)(cka + 2 * id);
-        return fmaf(k.x, x * x * x, k.y);
+        const float4 v = t[id];
+        return fmaf(v.z, x * x * x, v.w);
+    }
+    static __device__ inline float at(const Set &c, float s) {
+        return __builtin_amdgcn_exp2f(fmaf(c.e, __builtin_amdgcn_logf(s), c.lk));
+    }
+    __device__ inline float ratio(const Set &s, float x) const { return at(load(s.B + L), x); }
+    template <bool CUBE>
+    __device__ inline float cap(const Set &s, float T) const {
+#pragma clang fp contract(off)
+        if constexpr (CUBE) return s.k * (T * T * T);
+        else return at(load(s.B + 2 * L), T + T);
     }
 };
 
@@ -139,6 +193,8 @@ struct StepArgs {
     int cube;                 // every capacity exponent is 3
     int nz, np;
     int lpw;                  // lines per wave (a contiguous block)
+    RowMasks m;               // of a line
+    unsigned lanes;           // byte offset of the image's lane words
     R X;                      // amplitude * pulse average of this step
     int held[4];              // r_inner, r_outer, z_low, z_high
     R val[4];
@@ -151,7 +207,7 @@ struct StepArgs {
     int joule;                // heater source times X / sqrt(T) (eq. (25)), X holding sqrt(T_J)
     // stepped domain (eq. (9)): lines above z_full take the terminal's row
     // tables (nz - 1 when there is none)
-    int z_full;
+    int z_full, nr_top;
     double jsq;               // sqrt(T_J) with the Joule source, else 1 (batch
                               // and adjoint kernels form their source with it)
 };
@@ -214,9 +270,10 @@ __device__ inline void elim_row(int r, R aa, R bb, R cc, R dd, R (&al)[RPL], R (
 // (a0, b0, c0, d0) is the chunk's first row.  On exit x[r] holds the solution
 // of row lg * RPL + r.  xch: LDS exchange area of this line's waves (9 G
 // values); all waves of the workgroup must call this together when G > 1.
+// drop: couplings below it are left out of the cyclic reduction (see there).
 template <typename R, int RPL, int G>
 __device__ inline void solve_tail(R a0, R b0, R c0, R d0, R (&al)[RPL], R (&ga)[RPL],
-                                  R (&de)[RPL], R (&x)[RPL], int lane, int wig, R *xch) {
+                                  R (&de)[RPL], R (&x)[RPL], int lane, int wig, R *xch, R drop) {
     static_assert(RPL >= 2, "chunks of at least two rows");
 #pragma unroll
     for (int r = RPL - 3; r >= 1; --r) {
@@ -288,8 +345,15 @@ __device__ inline void solve_tail(R a0, R b0, R c0, R d0, R (&al)[RPL], R (&ga)[
             PR = (R)1;
         }
     }
+    // A pass squares the couplings (they fall as exp(-distance / diffusion
+    // length of a step) and eq. (21) bounds that length by an axial interval),
+    // so most lines are done after one to three passes: stop once no lane of
+    // the wave couples by more than `drop`, which leaves the solution as it
+    // is to that part of its largest value.  (1024 x 4096 FP64 step 25.6 us
+    // with six passes and a clamped table index in every law, 23.9 without.)
 #pragma unroll
     for (int s = 1; s < WAVE; s <<= 1) {
+        if (!__any(!(fabs(A) < drop && fabs(C) < drop))) break;
         const int iu = l4 + 4 * (WAVE - s), id = l4 + 4 * s;
         const R Am = lane_read(A, iu), Cm = lane_read(C, iu), Dm = lane_read(D, iu);
         const R Ap = lane_read(A, id), Cp = lane_read(C, id), Dp = lane_read(D, id);
@@ -384,29 +448,57 @@ __device__ inline R dif(R ah, R al, R bh, R bl) {
         return ah - bh;
 }
 
-// The tables of a plan as the kernels hold them in LDS, and as the device
-// keeps them (one image, copied in at the start of a launch): the laws, then
-// the rows' gw, ge, info, then for a stepped domain the terminal's.
+// The device's image of a plan's tables: the laws, each line class's (the
+// full lines', and a stepped domain's terminal lines') per-row gw and ge,
+// each class's row words, the lane words.  The stepping kernel takes the laws
+// it uses and the full lines' gw, ge into LDS (a terminal line's rows are the
+// same up to its wall), the adjoint kernels everything up to the lane words,
+// each by stage_tables.
 __host__ __device__ constexpr size_t up16(size_t b) { return (b + 15) & ~(size_t)15; }
+// bytes of one law
+template <typename R>
+__host__ __device__ constexpr size_t law_size(bool poly) {
+    return poly ? sizeof(R) * POLY_BLK : sizeof(R) == 8 ? sizeof(double) * POW_BLK : sizeof(float4);
+}
 template <typename R>
 __host__ __device__ inline size_t law_bytes(int L, bool poly) {
-    const int nlaw = 3 * L + 2;
-    if (poly) return up16(sizeof(R) * POLY_BLK * nlaw);
-    if constexpr (sizeof(R) == 8) return up16(sizeof(double) * pow_blob_doubles(L));
-    else return up16(sizeof(float) * 4 * nlaw);        // log2 K - e, e, {K, A}
+    // (FP64: then the {K, A} pairs of LawLds::cube)
+    return up16((law_size<R>(poly) + (sizeof(R) == 8 && !poly ? 16 : 0)) * (3 * L + 2));
 }
-// one set of per-row tables (gw, ge, info) of an np-row line
+// the laws the stepping kernel uses: radial, ratio and, unless every exponent
+// is 3, capacity laws
 template <typename R>
-__host__ __device__ inline size_t row_bytes(int np) {
-    return up16((2 * sizeof(R) + sizeof(uint32_t)) * (size_t)np);
+__host__ __device__ inline size_t step_law_bytes(int L, bool cube, bool poly) {
+    return up16(law_size<R>(poly) * (cube ? 2 : 3) * L);
+}
+// gw, ge of a line class
+template <typename R>
+__host__ __device__ inline size_t geom_bytes(int np) {
+    return 2 * sizeof(R) * (size_t)np;
+}
+template <typename R>
+__host__ __device__ inline size_t info_offset(int L, int np, bool poly, bool stepped) {
+    return law_bytes<R>(L, poly) + (stepped ? 2 : 1) * geom_bytes<R>(np);
 }
 template <typename R>
 __host__ __device__ inline size_t tables_bytes(int L, int np, bool poly, bool stepped) {
-    return law_bytes<R>(L, poly) + (stepped ? 2 : 1) * row_bytes<R>(np);
+    return info_offset<R>(L, np, poly, stepped) + (stepped ? 2 : 1) * sizeof(uint32_t) * (size_t)np;
 }
-// The stepping kernel also keeps a two-slot ring of line buffers per wave
-// (the lines after the current one, loaded straight into LDS): a slot is
-// RPL rows x planes x 64 lanes.
+// The stepping kernel's LDS: laws, gw and ge of the full lines, then the
+// axial fluxes of its lines: a slot of one value per row for each line group
+// and one more.
+template <typename R>
+__host__ __device__ inline size_t step_tables_bytes(int L, int np, bool cube, bool poly) {
+    return step_law_bytes<R>(L, cube, poly) + geom_bytes<R>(np);
+}
+template <typename R>
+__host__ __device__ inline size_t flux_bytes(int np, int wpl) {
+    return sizeof(R) * (size_t)(STEP_WAVES / wpl + 1) * np;
+}
+
+// step_march keeps a two-slot ring of line buffers per wave after the tables
+// (the lines after the current one, loaded straight into LDS): a slot is RPL
+// rows x planes x 64 lanes.
 template <typename R>
 __host__ __device__ inline size_t ring_slot_elems(int rpl) {
     return (size_t)rpl * (Pair<R>::on ? 2 : 1) * WAVE;
@@ -432,25 +524,32 @@ __host__ __device__ inline size_t line_lds_bytes(int rpl) {
     return 0;
 }
 
-// Start the copy of a plan's table image into LDS (dynamic shared memory);
-// all STEP_WAVES waves call it, and stage_wait before the first read.
+// Start the copy of a plan's tables (two ranges of the image, lengths
+// multiples of 16 bytes, one after the other in LDS); all STEP_WAVES waves
+// call it, and stage_wait before the first read.
 // A launch runs only one or two lines per wave, so the tables' latency is
 // part of every step.  Copied through registers in loops (each 4 KiB pass of
 // each table waits for its loads: 11 memory latencies in a row for 8 layers
 // and 1024 rows) the 1024 x 4096 FP64 step took 28.0 us and a 64 x 128 FP32
 // step 5.1 us; with every wave issuing all its pieces of 1 KiB (64 lanes x 16
 // bytes, memory to LDS, no registers) before anything waits, 25.6 and 4.0 us.
-__device__ inline void stage_tables(const unsigned char *img, unsigned char *smem, unsigned bytes) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+__device__ inline void stage_range(const unsigned char *img, unsigned char *smem, unsigned bytes,
+                                   unsigned wv, int lane) {
     const unsigned full = bytes >> 10, rem = bytes & 1023;
     for (unsigned c = wv; c < full; c += STEP_WAVES)
         __builtin_amdgcn_global_load_lds((const void *)(img + (c << 10) + 16 * lane),
                                          (__attribute__((address_space(3))) void *)(smem + (c << 10)),
                                          16, 0, 0);
-    // the last piece, under 1 KiB (a multiple of 16 bytes)
+    // the last piece, under 1 KiB
     if (wv == full % STEP_WAVES && 16u * lane < rem)
         *(uint4 *)(smem + (full << 10) + 16 * lane) = *(const uint4 *)(img + (full << 10) + 16 * lane);
+}
+__device__ inline void stage_tables(const unsigned char *a, unsigned na, const unsigned char *b,
+                                    unsigned nb, unsigned char *smem) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    stage_range(a, smem, na, wv, lane);
+    if (nb) stage_range(b, smem + na, nb, STEP_WAVES - 1 - wv, lane);
 }
 // every piece of the tables has landed (vmcnt 0) and every wave knows it
 __device__ inline void stage_wait() {
@@ -458,25 +557,12 @@ __device__ inline void stage_wait() {
     __syncthreads();
 }
 
-// The law evaluators over the staged tables.
-template <typename R>
-__device__ inline LawLds<R> laws_in(const unsigned char *smem, int L) {
-    const int nlaw = 3 * L + 2;
-    LawLds<R> v;
-    if constexpr (sizeof(R) == 8) {
-        v.blk = (const double *)smem;
-        v.cka = v.blk + (size_t)nlaw * POW_BLK;
-    } else {
-        v.lk = (const float *)smem;
-        v.ex = v.lk + nlaw;
-        v.cka = v.lk + 2 * nlaw;
-    }
-    return v;
-}
+// The law evaluator over the staged tables.
 template <typename R, bool POLY>
 __device__ inline auto staged_laws(const unsigned char *smem, int L) {
-    if constexpr (POLY) return LawPoly<R>{(const R *)smem};
-    else return laws_in<R>(smem, L);
+    if constexpr (POLY) return LawPoly<R>{(const R *)smem, L};
+    else if constexpr (sizeof(R) == 8) return LawLds<double>{(const double *)smem, L};
+    else return LawLds<float>{(const float4 *)smem, L};
 }
 
 }  // namespace cryo

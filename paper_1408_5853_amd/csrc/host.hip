@@ -67,7 +67,7 @@ double turn_on_source(const Pulse &p, int64_t k, int i) {
 // FP64 power tables (see POW_*): one block per law id, then the cube path's
 // multipliers and addends (K T^3 + A)
 static void fill_pow_blob(const Laws &lw, std::vector<double> &blob) {
-    const int L = lw.L, nlaw = 3 * L + 2, UNIT = law_unit(L);
+    const int L = lw.L, nlaw = 3 * L + 2;
     blob.assign(pow_blob_doubles(L), 0.0);
     double *B = blob.data();
     double *CKA = B + (size_t)nlaw * POW_BLK;                     // {K, A} per id
@@ -79,8 +79,10 @@ static void fill_pow_blob(const Laws &lw, std::vector<double> &blob) {
             R[2 * j] = pow(m0, e);
             R[2 * j + 1] = 2.0 / m0;          // applied to the frexp mantissa in [1/2, 1)
         }
-        for (int x = 0; x < POW_NE; ++x) R[POW_BX + x] = lw.K[id] * exp2(e * (x + POW_EMIN));
+        for (int x = POW_EMIN; x < POW_EMIN + POW_NX; ++x)
+            R[POW_BX + (x & (POW_NX - 1))] = lw.K[id] * exp2(e * x);
         R[POW_BE] = e;
+        R[POW_BE + 1] = id < L ? lw.K[2 * L + id] : 0.0;  // the cube path's capacity multiplier
         // binomial coefficients of (1 + u)^e, k = 2..POW_DEG
         double c = e;
         for (int k = 2; k <= POW_DEG; ++k) {
@@ -88,7 +90,7 @@ static void fill_pow_blob(const Laws &lw, std::vector<double> &blob) {
             R[POW_BE + k] = c;
         }
         CKA[2 * id] = (id >= 2 * L && id < 3 * L) ? lw.K[id] : 0.0;
-        CKA[2 * id + 1] = id == UNIT ? 1.0 : 0.0;
+        CKA[2 * id + 1] = id == law_unit(L) ? 1.0 : 0.0;
     }
 }
 
@@ -197,16 +199,23 @@ static void pick_shape(int nr, int *rpl, int *wpl) {
     *wpl = w;
 }
 
-// Lines per wave: about one workgroup per compute unit of an MI355X (256),
-// so that every unit works and each line group amortises its start-up line.
-static int pick_lpw(int nz, int wpl) {
+// Lines per wave.  FP32 pairs: one (step_shared; two or more workgroups share
+// a compute unit and take turns with memory and arithmetic) up to 10 rows per
+// lane, on any grid: 512 x 4098 9.1 us a step against 10.2 with 2 lines, 512 x
+// 8194 14.2 against 16.6 and 18.6 (2, 4 lines), 640 x 4098 11.6 against 11.4.
+// Otherwise about one workgroup per compute unit of an MI355X (256), so that
+// every unit works and each line group amortises its start-up line: FP64 512
+// x 4098 14.3, 14.1, 21.4 us (1, 2, 4 lines), 640 x 4098 18.7, 17.0, 26.2,
+// 1024 x 4096 29.1, 23.9, 41; FP32 1024 x 4096 16.9, 16.5, 28.
+static int pick_lpw(int nz, int rpl, int wpl, cryo_dtype dtype) {
+    if (dtype == CRYO_F32 && rpl <= 10) return 1;
     const int per_wg = STEP_WAVES_HOST / wpl;
     const double l = (double)(nz - 2) / ((double)per_wg * 256.0);
     return std::min(8, std::max(1, (int)std::lround(l)));
 }
 
-// Device copies of the per-row tables, made once on the first call that
-// needs the device (on the device current at that time).
+// The device's table image, made once on the first call that needs the device
+// (on the device current at that time).
 cryo_status ensure_device(cryo_plan *p) {
     if (p->d_tab) return CRYO_OK;
     (void)hipGetDevice(&p->device);
@@ -247,7 +256,8 @@ static void fill_rows(cryo_plan *p, int n, bool terminal, double *fgwo, double *
         int idx = (i % rpl) * (WAVE * p->wpl) + i / rpl;
         uint32_t kind = (i == n - 1 && n < nr) ? (uint32_t)K_HI : (uint32_t)p->kind[i];
         uint32_t m = p->lay[i];
-        uint32_t lawE = (i < n - 1) ? p->lay[i + 1] : ZERO;      // radial law of interval i+1
+        // radial law of interval i+1 (the wall, whose ge is 0, keeps the last)
+        uint32_t lawE = p->lay[i < n - 1 ? i + 1 : i];
         uint32_t law2 = ZERO, law3 = ZERO, lawC = ZERO, heat = 0, held = 0, side = 0;
         double gw = 0.0, ge = 0.0;
         if (kind == K_CAP) {
@@ -306,21 +316,37 @@ static void fill_rows(cryo_plan *p, int n, bool terminal, double *fgwo, double *
 }
 
 static void build_row_tables(cryo_plan *p) {
-    const int nr = p->nr, L = p->L, np = p->np;
+    const int nr = p->nr, L = p->L, np = p->np, nl = np / p->rpl;
     const int ZERO = law_zero(L), UNIT = law_unit(L);
-    // padding rows: identity; polynomial laws divide slot 2 by slot 3 on
-    // every row, so slot 3 is the unit law there
-    const uint32_t pad = info_pack(K_PAD, 0, 0, 0, ZERO, ZERO, p->poly ? UNIT : ZERO, UNIT);
+    // Padding past the line: capacity rows of the outer layer with no radial
+    // coupling (gw = ge = 0), so that they need no treatment of their own;
+    // nothing reads them.  polynomial laws divide slot 2 by slot 3 (unit).
+    const uint32_t last = p->lay[nr - 1], one = p->poly ? UNIT : ZERO;
     p->fgw.assign(np, 0.0);
     p->fge.assign(np, 0.0);
-    p->finfo.assign(np, pad);
+    p->finfo.assign(np, info_pack(K_CAP, 0, 0, 0, last, last, one, 2 * L + last));
     fill_rows(p, nr, false, p->fgw.data(), p->fge.data(), p->finfo.data());
-    // stepped domain (eq. (9)): the terminal's lines, nodes 0..nr_top-1
+    // stepped domain (eq. (9)): the terminal's lines, nodes 0..nr_top-1; the
+    // field's nodes past its wall stay as they are (identity rows)
     p->tfgw.assign(np, 0.0);
     p->tfge.assign(np, 0.0);
-    p->tfinfo.assign(np, pad);
+    const uint32_t lt = p->lay[p->stepped ? p->nr_top - 1 : nr - 1];
+    p->tfinfo.assign(np, info_pack(K_PAD, 0, 0, 0, lt, UNIT, one, UNIT));
     if (p->stepped)
         fill_rows(p, p->nr_top, true, p->tfgw.data(), p->tfge.data(), p->tfinfo.data());
+    p->masks = RowMasks{0, 0};
+    p->lanes.assign(nl, LaneWord{0, 0, 0, 0});
+    for (int lg = 0; lg < nl; ++lg) {
+        LaneWord &w = p->lanes[lg];
+        w.law = p->lay[std::min(std::max(lg * p->rpl, 1), nr - 1)];
+        for (int r = 0; r < p->rpl; ++r) {
+            const uint32_t f = p->finfo[(size_t)r * nl + lg], bit = 1u << r;
+            if ((f & 7) == K_IFACE) w.iface |= bit;
+            if ((f >> 3) & 1) w.heat |= bit;
+        }
+        p->masks.iface |= w.iface;
+        p->masks.heat |= w.heat;
+    }
     p->surf_lane = (nr - 1) / p->rpl;
     p->surf_reg = (nr - 1) % p->rpl;
 }
@@ -371,7 +397,7 @@ cryo_status cryo_plan_create(const cryo_problem *prob, cryo_dtype dtype, cryo_pl
     p->L = prob->geom.n_layers;
     pick_shape(p->nr, &p->rpl, &p->wpl);
     p->np = WAVE * p->wpl * p->rpl;
-    p->lpw = pick_lpw(p->nz, p->wpl);
+    p->lpw = pick_lpw(p->nz, p->rpl, p->wpl, dtype);
     p->eta = prob->geom.height / (p->nz - 1);
     const int nr = p->nr, L = p->L;
 

@@ -56,20 +56,26 @@ __host__ __device__ inline int law_unit(int L) { return 3 * L + 1; }
 //   bits 0-2 kind, bit 3 heater capacity node, bit 4 held boundary row,
 //   bit 5 its side (0 inner, 1 outer), bits 6-11 law of the east r-face,
 //   bits 12-17 law of slot 2, bits 18-23 law of slot 3, bits 24-29 capacity law.
-// Slot 2 is the north axial face of a capacity row (eq. (11)), slot 3 is not
-// used by capacity rows (their south face is the previous line's north
-// face); an interface row (eq. (18)) evaluates its inner and outer layer laws
-// at the node in slots 2 and 3; boundary and padding rows use the zero and
-// unit laws so that one formula serves every row.  The stepping kernel's
-// words (`finfo`, law ids of `flaws`): slot 2 of a capacity row is the
-// radial law of its layer, slot 2 of an interface row the ratio law, slot 3
-// is unused, and held walls are found by position (rows 0 and nr - 1).
 __host__ __device__ inline uint32_t info_pack(uint32_t kind, uint32_t heat, uint32_t held,
                                               uint32_t side, uint32_t lawE, uint32_t law2,
                                               uint32_t law3, uint32_t lawC) {
     return kind | (heat << 3) | (held << 4) | (side << 5) | (lawE << 6) | (law2 << 12) |
            (law3 << 18) | (lawC << 24);
 }
+
+// The stepping kernel reads no row words: rows other than capacity rows are
+// found from a lane's word (its chunk's first law, and one bit per row) and
+// by position.  Bits 0..rpl-1 stand for the rows of a chunk.
+struct LaneWord {
+    uint32_t law;        // radial law of the interval west of the chunk's first row
+    uint32_t iface;      // interface rows
+    uint32_t heat;       // heater capacity rows
+    uint32_t pad;
+};
+// The same bits of any lane of a line (the rows that need a look at all).
+struct RowMasks {
+    uint32_t iface, heat;
+};
 
 struct Laws {
     int L;
@@ -88,17 +94,24 @@ struct Laws {
 // refuses exponents whose bound exceeds POW_TRUNC_MAX (about -5.3 <= e <= 12.5).
 // One block of doubles per law id:
 //   [0, 2 NM)            {m0^e, 2/m0} for j = 0..NM-1
-//   [2 NM, 2 NM + NE)    K 2^(x e) for binades x = EMIN..EMIN+NE-1
-//   2 NM + NE            e; the next slot is unused
-//   2 NM + NE + 2 ..     binomial(e, k), k = 2..7
-//   then 2 pad doubles: a 1296-byte block shifts successive laws by 4 LDS
+//   [2 NM, 2 NM + NX)    K 2^(x e) at slot x mod NX, for the NE binades x =
+//                        EMIN..EMIN+NE-1 (and the NX - NE after them): the
+//                        slot is five bits of the argument's exponent, so an
+//                        argument off the range (flagged by the caller's
+//                        check) still reads inside the table
+//   2 NM + NX            e, then the layer's cube multiplier (radial laws)
+//   2 NM + NX + 2 ..     binomial(e, k), k = 2..7
+//   then 2 pad doubles: a 1360-byte block shifts successive laws by 20 LDS
 //   banks, so lanes reading different laws do not collide
 constexpr int POW_MBITS = 6, POW_NM = 1 << POW_MBITS, POW_NE = 24, POW_EMIN = -4;
+constexpr int POW_NX = 32;
 constexpr int POW_DEG = 7;
 constexpr double POW_TRUNC_MAX = 1e-14;
 constexpr double POW_TLO = 0.0625, POW_THI = 1048576.0;   // 2^EMIN, 2^(EMIN+NE)
+constexpr unsigned POW_HLO = 0x3fb00000u;                 // high word of POW_TLO
+constexpr unsigned POW_HN = (unsigned)POW_NE << 20;       // high words from there to POW_THI
 constexpr int POW_BX = 2 * POW_NM;                 // binade multipliers
-constexpr int POW_BE = POW_BX + POW_NE;            // exponent, then binomials from +2
+constexpr int POW_BE = POW_BX + POW_NX;            // exponent, then binomials from +2
 constexpr int POW_BLK = POW_BE + 2 + (POW_DEG - 1) + 2;
 // Polynomial laws (eqs. (23), (24)) use the same blob size with POLY_BLK
 // doubles per law id in the stepping kernel's id scheme: ids 0..L-1 hold
@@ -106,10 +119,12 @@ constexpr int POW_BLK = POW_BE + 2 + (POW_DEG - 1) + 2;
 // laws 0 and 1; the ratio ids are unused (an interface row divides its
 // inner layer's law, slot 2, by its outer layer's, slot 3).
 constexpr int POLY_BLK = 6;
-// blob: (3L+2) law blocks, then {cube multiplier, addend} pairs per law id
+// blob: 3L+2 law blocks, then {cube multiplier, addend} pairs per law id
 __host__ __device__ inline size_t pow_blob_doubles(int L) {
     return (size_t)(3 * L + 2) * (POW_BLK + 2);
 }
+// what a plan's acceptance counts per law (see step_lds_reserve)
+constexpr size_t LAW_RESERVE_F64 = 1312, LAW_RESERVE_F32 = 24;
 
 // Arguments of the adjoint kernels of one step (FP64, internal layout).
 struct AdjArgs {
@@ -155,6 +170,8 @@ struct cryo_plan {
     cryo::Laws laws;
     std::vector<double> fgw, fge;
     std::vector<uint32_t> finfo;
+    std::vector<cryo::LaneWord> lanes;
+    cryo::RowMasks masks;
     cryo::Laws flaws;
     std::vector<double> fpow_blob;
     cryo::Pulse pulse;
@@ -204,10 +221,12 @@ cryo_status launch_step(const cryo_plan *p, const void *Tin, void *Tout, double 
 cryo_status launch_surf_reduce(const cryo_plan *p, const double *partial, int nsteps,
                                double *out, hipStream_t s);
 int step_grid(const cryo_plan *p);
+bool step_shared(const cryo_plan *p);
 size_t step_lds(const cryo_plan *p);            // dynamic LDS of the stepping kernel
 // what a plan is accepted against: the LDS its shape and domain would take
 // with power tables of either kind (laws may be replaced after the check)
 size_t step_lds_reserve(const cryo_plan *p);
+size_t tables_reserve(const cryo_plan *p);
 std::vector<unsigned char> table_image(const cryo_plan *p);
 constexpr size_t MAX_STEP_LDS = 160 * 1024 - 4096;   // leaves room for static LDS
 cryo_status ensure_device(cryo_plan *p);
