@@ -36,9 +36,14 @@ struct cryo_batch {
     cryo_dtype dtype;
     std::vector<int64_t> off;        // element offsets of the instances' fields
     std::vector<cryo::Bucket> buckets;
-    void *d_block = nullptr;         // descriptors and workgroup maps
+    void *d_block = nullptr;         // descriptors, workgroup maps, conversion tables
     size_t block_bytes = 0;
     std::vector<unsigned char> h_block;
+    // layout conversions: byte offsets of the instances and of their first
+    // lines (n + 1) in the block, all lines, and the widest line's LDS rows
+    size_t conv_off = 0, first_off = 0;
+    int64_t lines = 0;
+    int conv_rows = 0;
     // workspace layout
     std::vector<size_t> ws_field;    // per instance: offset of its two internal buffers
     size_t ws_bytes = 0;
@@ -64,6 +69,9 @@ void step_desc_fill(const cryo_plan *p, void *out, void *buf0, void *buf1, int *
 cryo_status launch_step_batch(cryo_dtype dt, int rpl, int wpl, bool cube, bool poly,
                               bool stepped, bool shared, const void *desc, const int2 *map,
                               int nwg, size_t lds, int64_t n, const int64_t *k0, hipStream_t s);
+cryo_status launch_batch_convert(cryo_dtype dt, bool in, const BatchConv *inst,
+                                 const int64_t *first, int n, int64_t lines, int buf_rows, void *T,
+                                 int par, hipStream_t s);
 cryo_status launch_set_i64(int64_t *ptr, int64_t v, hipStream_t s);
 cryo_status launch_add_i64(int64_t *ptr, int64_t v, hipStream_t s);
 
@@ -132,8 +140,20 @@ static cryo_status batch_build_buckets(cryo_batch *b) {
         bk.map_off = o;
         o = align256(o + sizeof(int2) * bk.map.size());
     }
+    const size_t n = b->plans.size();
+    b->conv_off = o;
+    o = align256(o + sizeof(BatchConv) * n);
+    b->first_off = o;
+    o = align256(o + sizeof(int64_t) * (n + 1));
     b->block_bytes = o;
     b->h_block.assign(o, 0);
+    int64_t *first = (int64_t *)(b->h_block.data() + b->first_off);
+    for (size_t i = 0; i < n; ++i) {
+        const cryo_plan *p = b->plans[i];
+        first[i + 1] = first[i] + (int64_t)p->nz * (p->dtype == CRYO_F32 ? 2 : 1);
+        b->conv_rows = std::max(b->conv_rows, p->np + WAVE * p->wpl);
+    }
+    b->lines = first[n];
     for (Bucket &bk : b->buckets)
         memcpy(b->h_block.data() + bk.map_off, bk.map.data(), sizeof(int2) * bk.map.size());
     return CRYO_OK;
@@ -237,7 +257,6 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
     if (((uintptr_t)ws & 255) != 0) return fail(CRYO_ERR_WORKSPACE, "workspace must be 256-aligned");
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws;
-    const size_t es = b->dtype == CRYO_F64 ? 8 : 4;
     const int n = (int)b->plans.size();
     for (cryo_plan *p : b->plans) {
         cryo_status st = ensure_device(p);
@@ -260,17 +279,26 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
                 step_desc_fill(b->plans[i], b->h_block.data() + bk.desc_off + ds * q, f,
                                f + field_bytes_internal(b->plans[i]), (int *)w + i);
             }
+        BatchConv *conv = (BatchConv *)(b->h_block.data() + b->conv_off);
+        for (int i = 0; i < n; ++i) {
+            const cryo_plan *p = b->plans[i];
+            char *f = w + b->ws_field[i];
+            conv[i] = BatchConv{b->off[i], {f, f + field_bytes_internal(p)}, p->prob.T_init,
+                                p->nz, p->nr, p->np, p->rpl, WAVE * p->wpl, (int *)w + i};
+        }
         hipError_t e = hipMemcpy(b->d_block, b->h_block.data(), b->block_bytes,
                                  hipMemcpyHostToDevice);
         if (e != hipSuccess) return fail(CRYO_ERR_DEVICE, "batch descriptor upload");
     }
     int64_t *k0p = (int64_t *)(w + counter_off(b));
-    for (int i = 0; i < n; ++i) {
-        cryo_status st = launch_to_internal(b->plans[i], (char *)T + es * b->off[i],
-                                            w + b->ws_field[i], (int *)w + i, s);
-        if (st != CRYO_OK) return st;
-    }
-    cryo_status st = CRYO_OK;
+    auto convert = [&](bool in, int par) {
+        const char *blk = (const char *)b->d_block;
+        return launch_batch_convert(b->dtype, in, (const BatchConv *)(blk + b->conv_off),
+                                    (const int64_t *)(blk + b->first_off), n, b->lines,
+                                    b->conv_rows, T, par, s);
+    };
+    cryo_status st = convert(true, 0);
+    if (st != CRYO_OK) return st;
     // the steps of one bucket (its instances only) on stream strm: step
     // offsets first .. first + count - 1 from the device step counter
     auto launch_bucket = [&](const Bucket &bk, int64_t first, int64_t count,
@@ -418,14 +446,7 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
     st = regular(k0 + nsteps - k);
     if (st != CRYO_OK) return st;
     b->graph_ws = ws;
-    for (int i = 0; i < n; ++i) {
-        const cryo_plan *p = b->plans[i];
-        char *f = w + b->ws_field[i];
-        st = launch_from_internal(p, f + par * field_bytes_internal(p),
-                                  (char *)T + es * b->off[i], (int *)w + i, s);
-        if (st != CRYO_OK) return st;
-    }
-    return CRYO_OK;
+    return convert(false, par);
 }
 
 cryo_status cryo_batch_poll(const cryo_batch *b, const void *ws, void *stream, int32_t *bad) {

@@ -25,43 +25,139 @@ CRYO_STEP_EXTERN(float, false, true)
 CRYO_STEP_EXTERN(float, true, false)
 CRYO_STEP_EXTERN(float, true, true)
 
-// ABI field -> internal lines.  FP32 fields are two planes [2][nz][nr]
-// (rounded value, residual) and become [nz][2][np] internally.
+// Layout conversions: the ABI field (row major; FP32 two planes [2][nz][nr],
+// rounded value and residual) and the internal lines ([nz][np], FP32
+// [nz][2][np], lane-major).  One wave per line and plane: both sides are read
+// and written 64 rows at a time, and the wave turns the line over in LDS (one
+// element of padding per chunk, so that the chunks' rows fall on different
+// banks).  Bound by memory: 1024 x 4096 in and out 22 us FP64, 25 us FP32 pairs
+// (40 and 59 us with an element per thread, its other side a cache line apart
+// from its neighbour's, and 64-bit divisions); the 256-cell sweep's fields, one
+// launch each way, 0.66 ms (2.4 ms with a launch per cell).
+constexpr int CONV_WAVES = 4;
 template <typename R>
-__global__ void k_to_internal(const R *T, R *Ti, int nz, int nr, int np, int rpl, R pad,
-                              int *flag) {
-    constexpr int NPL = Pair<R>::on ? 2 : 1;
-    size_t n = (size_t)nz * NPL * np;
-    size_t start = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (start == 0 && flag) *flag = 0;
-    for (size_t idx = start; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
-        int j = (int)(idx / ((size_t)NPL * np));
-        int rem = (int)(idx % ((size_t)NPL * np));
-        int plane = rem / np, q = rem % np;
-        const int nl = np / rpl;                      // lanes per line
-        int i = (q % nl) * rpl + q / nl;
-        R v = plane == 0 ? pad : (R)0;
-        if (i < nr) v = T[((size_t)plane * nz + j) * nr + i];
-        Ti[idx] = v;
+struct ConvArgs {
+    R *T;              // ABI field
+    R *Ti;             // internal lines
+    int nz, nr, np, rpl, nl;
+    R pad;
+    int *flag;
+};
+template <typename R>
+__host__ __device__ constexpr int planes() { return Pair<R>::on ? 2 : 1; }
+__host__ __device__ inline int conv_lds_rows(int np, int nl) { return np + nl; }
+
+// line p = j planes + plane; buf: this wave's LDS
+template <typename R>
+__device__ inline void line_in(const ConvArgs<R> &c, int p, R *buf, int lane) {
+    constexpr int U = 8;
+    const int j = p / planes<R>(), plane = p % planes<R>();
+    const R *src = c.T + ((size_t)plane * c.nz + j) * c.nr;
+    R *dst = c.Ti + (size_t)p * c.np;
+    const R pad = plane == 0 ? c.pad : (R)0;
+    for (int i0 = lane; i0 < c.np; i0 += U * WAVE) {
+        R v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * WAVE;
+            v[u] = i < c.nr ? src[i] : pad;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * WAVE;
+            if (i < c.np) buf[i + i / c.rpl] = v[u];
+        }
     }
+    __builtin_amdgcn_wave_barrier();
+    // position q = reg nl + lg holds row lg rpl + reg
+    for (int lg = lane; lg < c.nl; lg += WAVE)
+        for (int r = 0; r < c.rpl; ++r) dst[r * c.nl + lg] = buf[lg * (c.rpl + 1) + r];
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <typename R>
-__global__ void k_from_internal(const R *Ti, R *T, int nz, int nr, int np, int rpl, int *flag) {
-    constexpr int NPL = Pair<R>::on ? 2 : 1;
-    size_t n = (size_t)NPL * nz * nr;
+__device__ inline int line_out(const ConvArgs<R> &c, int p, R *buf, int lane) {
+    constexpr int U = 8;
+    const int j = p / planes<R>(), plane = p % planes<R>();
+    const R *src = c.Ti + (size_t)p * c.np;
+    R *dst = c.T + ((size_t)plane * c.nz + j) * c.nr;
+    for (int lg = lane; lg < c.nl; lg += WAVE)
+        for (int r0 = 0; r0 < c.rpl; r0 += U) {
+            R v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = r0 + u < c.rpl ? src[(r0 + u) * c.nl + lg] : (R)0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (r0 + u < c.rpl) buf[lg * (c.rpl + 1) + r0 + u] = v[u];
+        }
+    __builtin_amdgcn_wave_barrier();
     int bad = 0;
-    for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < n;
-         idx += (size_t)gridDim.x * blockDim.x) {
-        int plane = (int)(idx / ((size_t)nz * nr));
-        size_t rem = idx % ((size_t)nz * nr);
-        int j = (int)(rem / nr), i = (int)(rem % nr);
-        const int nl = np / rpl;
-        R v = Ti[((size_t)j * NPL + plane) * np + (i % rpl) * nl + i / rpl];
-        T[idx] = v;
+    for (int i = lane; i < c.nr; i += WAVE) {
+        const R v = buf[i + i / c.rpl];
+        dst[i] = v;
         bad |= !isfinite(v);
     }
-    if (bad) atomicOr(flag, 1);
+    __builtin_amdgcn_wave_barrier();
+    return bad;
+}
+
+template <typename R>
+__global__ __launch_bounds__(CONV_WAVES *WAVE) void k_to_internal(ConvArgs<R> c) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    R *buf = (R *)smem + (size_t)wv * conv_lds_rows(c.np, c.nl);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && c.flag) *c.flag = 0;
+    for (int p = blockIdx.x * CONV_WAVES + wv; p < c.nz * planes<R>(); p += gridDim.x * CONV_WAVES)
+        line_in(c, p, buf, lane);
+}
+
+template <typename R>
+__global__ __launch_bounds__(CONV_WAVES *WAVE) void k_from_internal(ConvArgs<R> c) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    R *buf = (R *)smem + (size_t)wv * conv_lds_rows(c.np, c.nl);
+    int bad = 0;
+    for (int p = blockIdx.x * CONV_WAVES + wv; p < c.nz * planes<R>(); p += gridDim.x * CONV_WAVES)
+        bad |= line_out(c, p, buf, lane);
+    if (bad) atomicOr(c.flag, 1);
+}
+
+// The same for every instance of a batch in one launch: line numbers run over
+// the instances (first[i] .. first[i + 1] - 1), each wave takes a contiguous
+// run of them.
+template <typename R, bool IN>
+__global__ __launch_bounds__(CONV_WAVES *WAVE) void k_batch_convert(const BatchConv *inst,
+                                                                    const int64_t *first, int n,
+                                                                    R *T, int par, int buf_rows) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    R *buf = (R *)smem + (size_t)wv * buf_rows;
+    if constexpr (IN)
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+            *inst[i].flag = 0;
+    const int64_t waves = (int64_t)gridDim.x * CONV_WAVES, w = blockIdx.x * CONV_WAVES + wv;
+    const int64_t total = first[n], per = (total + waves - 1) / waves;
+    int64_t p = w * per;
+    const int64_t end = min(p + per, total);
+    if (p >= end) return;
+    int lo = 0, hi = n;                          // the instance of line p
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (first[mid] <= p) lo = mid;
+        else hi = mid;
+    }
+    for (int i = lo; p < end; ++i) {
+        const BatchConv b = inst[i];
+        const ConvArgs<R> c = {T + b.off, (R *)b.buf[par], b.nz, b.nr, b.np, b.rpl, b.nl,
+                               (R)b.pad, b.flag};
+        const int64_t stop = min(end, first[i + 1]);
+        int bad = 0;
+        for (; p < stop; ++p) {
+            if constexpr (IN) line_in(c, (int)(p - first[i]), buf, lane);
+            else bad |= line_out(c, (int)(p - first[i]), buf, lane);
+        }
+        if (bad) atomicOr(c.flag, 1);
+    }
 }
 
 template <typename R>
@@ -71,13 +167,15 @@ __global__ void k_fill(R *T, size_t n, R v, size_t n_lo) {
         T[idx] = idx < n ? v : (R)0;
 }
 
-// S[k] = sum over workgroups of the step-k partial sums, in a fixed order
-__global__ void k_surf_reduce(const double *part, int nsteps, int G, double *out) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nsteps) return;
+// S[k] = sum over workgroups of the step-k partial sums, a wave per step: each
+// lane its strided terms in order, then a fixed tree (one thread per step
+// waited for its G loads in a row)
+__global__ __launch_bounds__(WAVE) void k_surf_reduce(const double *part, int G, double *out) {
+    const int k = blockIdx.x;
     double s = 0.0;
-    for (int g = 0; g < G; ++g) s += part[(size_t)k * G + g];
-    out[k] = s;
+    for (int g = threadIdx.x; g < G; g += WAVE) s += part[(size_t)k * G + g];
+    for (int w = WAVE / 2; w > 0; w >>= 1) s += __shfl_down(s, w, WAVE);
+    if (threadIdx.x == 0) out[k] = s;
 }
 
 static int blocks_for(size_t n) {
@@ -101,30 +199,57 @@ int step_grid(const cryo_plan *p) {
 }
 
 template <typename R>
-static cryo_status to_internal_t(const cryo_plan *p, const void *T, void *Ti, int *flag,
-                                 hipStream_t s) {
-    size_t n = (size_t)p->nz * p->np * (Pair<R>::on ? 2 : 1);
-    hipLaunchKernelGGL(k_to_internal<R>, dim3(blocks_for(n)), dim3(256), 0, s, (const R *)T,
-                       (R *)Ti, p->nz, p->nr, p->np, p->rpl, (R)p->prob.T_init, flag);
-    return launch_check("to_internal");
+static ConvArgs<R> conv_args(const cryo_plan *p, const void *T, const void *Ti, int *flag) {
+    return ConvArgs<R>{(R *)T, (R *)Ti, p->nz, p->nr, p->np, p->rpl, WAVE * p->wpl,
+                       (R)p->prob.T_init, flag};
+}
+template <typename R>
+static void launch_convert(const cryo_plan *p, bool in, const void *T, const void *Ti, int *flag,
+                           hipStream_t s) {
+    const ConvArgs<R> c = conv_args<R>(p, T, Ti, flag);
+    const int lines = c.nz * planes<R>();
+    const dim3 g(std::min((lines + CONV_WAVES - 1) / CONV_WAVES, 65536)), b(CONV_WAVES * WAVE);
+    const size_t lds = sizeof(R) * CONV_WAVES * conv_lds_rows(c.np, c.nl);
+    if (in) hipLaunchKernelGGL(k_to_internal<R>, g, b, lds, s, c);
+    else hipLaunchKernelGGL(k_from_internal<R>, g, b, lds, s, c);
 }
 
 cryo_status launch_to_internal(const cryo_plan *p, const void *T, void *Ti, int *flag,
                                hipStream_t s) {
-    return p->dtype == CRYO_F64 ? to_internal_t<double>(p, T, Ti, flag, s)
-                                : to_internal_t<float>(p, T, Ti, flag, s);
+    if (p->dtype == CRYO_F64) launch_convert<double>(p, true, T, Ti, flag, s);
+    else launch_convert<float>(p, true, T, Ti, flag, s);
+    return launch_check("to_internal");
 }
 
 cryo_status launch_from_internal(const cryo_plan *p, const void *Ti, void *T, int *flag,
                                  hipStream_t s) {
-    size_t n = (size_t)p->nz * p->nr * (p->dtype == CRYO_F32 ? 2 : 1);
-    if (p->dtype == CRYO_F64)
-        hipLaunchKernelGGL(k_from_internal<double>, dim3(blocks_for(n)), dim3(256), 0, s,
-                           (const double *)Ti, (double *)T, p->nz, p->nr, p->np, p->rpl, flag);
-    else
-        hipLaunchKernelGGL(k_from_internal<float>, dim3(blocks_for(n)), dim3(256), 0, s,
-                           (const float *)Ti, (float *)T, p->nz, p->nr, p->np, p->rpl, flag);
+    if (p->dtype == CRYO_F64) launch_convert<double>(p, false, T, Ti, flag, s);
+    else launch_convert<float>(p, false, T, Ti, flag, s);
     return launch_check("from_internal");
+}
+
+// a batch's fields between the caller's packed buffer T and the instances'
+// internal buffers `par`
+cryo_status launch_batch_convert(cryo_dtype dt, bool in, const BatchConv *inst,
+                                 const int64_t *first, int n, int64_t lines, int buf_rows, void *T,
+                                 int par, hipStream_t s) {
+    // up to 16 waves a compute unit, one line each at least
+    const dim3 g((unsigned)std::min<int64_t>((lines + CONV_WAVES - 1) / CONV_WAVES, 4096));
+    const dim3 b(CONV_WAVES * WAVE);
+    const size_t lds = (dt == CRYO_F64 ? 8 : 4) * (size_t)CONV_WAVES * buf_rows;
+    if (dt == CRYO_F64 && in)
+        hipLaunchKernelGGL((k_batch_convert<double, true>), g, b, lds, s, inst, first, n,
+                           (double *)T, par, buf_rows);
+    else if (dt == CRYO_F64)
+        hipLaunchKernelGGL((k_batch_convert<double, false>), g, b, lds, s, inst, first, n,
+                           (double *)T, par, buf_rows);
+    else if (in)
+        hipLaunchKernelGGL((k_batch_convert<float, true>), g, b, lds, s, inst, first, n,
+                           (float *)T, par, buf_rows);
+    else
+        hipLaunchKernelGGL((k_batch_convert<float, false>), g, b, lds, s, inst, first, n,
+                           (float *)T, par, buf_rows);
+    return launch_check("batch convert");
 }
 
 cryo_status launch_fill(const cryo_plan *p, void *T, hipStream_t s) {
@@ -207,8 +332,7 @@ cryo_status launch_step(const cryo_plan *p, const void *Tin, void *Tout, double 
 
 cryo_status launch_surf_reduce(const cryo_plan *p, const double *partial, int nsteps,
                                double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_surf_reduce, dim3((nsteps + 255) / 256), dim3(256), 0, s, partial,
-                       nsteps, step_grid(p), out);
+    hipLaunchKernelGGL(k_surf_reduce, dim3(nsteps), dim3(WAVE), 0, s, partial, step_grid(p), out);
     return launch_check("surf_reduce");
 }
 

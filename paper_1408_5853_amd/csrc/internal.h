@@ -141,6 +141,15 @@ struct AdjArgs {
     double xs;              // scale of the capacity rows (eta^2): the source's too
 };
 
+// One instance of a batch as the layout conversions see it.
+struct BatchConv {
+    int64_t off;            // its field's first element in the packed buffer
+    void *buf[2];           // its internal buffers
+    double pad;
+    int nz, nr, np, rpl, nl;
+    int *flag;
+};
+
 struct Pulse {      // in step units, snapped
     double b0, W, P;
     double amplitude;
