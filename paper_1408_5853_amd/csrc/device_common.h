@@ -202,6 +202,7 @@ struct StepArgs {
     int *flag;                // error word: bit 1 = temperature off the law tables
     double wz_end, wz_mid;    // trapezoid weights of the surface mean
     int surf_lane, surf_reg;
+    int surf_cols;            // partial sums: one per line (its count), or 0: per workgroup
     int groups;               // workgroups of one step of this instance
     Pulse pulse;              // batch: schedule evaluated on the device
     int joule;                // heater source times X / sqrt(T) (eq. (25)), X holding sqrt(T_J)
@@ -210,6 +211,13 @@ struct StepArgs {
     int z_full, nr_top;
     double jsq;               // sqrt(T_J) with the Joule source, else 1 (batch
                               // and adjoint kernels form their source with it)
+};
+
+// The steps of one launch: their sources (amplitude * pulse average).
+template <typename R>
+struct MultiRun {
+    int K;
+    R X[MULTI_MAX];
 };
 
 constexpr int STEP_WAVES = STEP_WAVES_HOST;

@@ -24,6 +24,14 @@ CRYO_STEP_EXTERN(float, false, false)
 CRYO_STEP_EXTERN(float, false, true)
 CRYO_STEP_EXTERN(float, true, false)
 CRYO_STEP_EXTERN(float, true, true)
+#define CRYO_MULTI_EXTERN(R, STEPPED) \
+    template <> \
+    bool MultiLaunch<R, STEPPED>::step(int, int, dim3, size_t, hipStream_t, const StepArgs<R> &, \
+                                       const MultiRun<R> &);
+CRYO_MULTI_EXTERN(double, false)
+CRYO_MULTI_EXTERN(double, true)
+CRYO_MULTI_EXTERN(float, false)
+CRYO_MULTI_EXTERN(float, true)
 
 // Layout conversions: the ABI field (row major; FP32 two planes [2][nz][nr],
 // rounded value and residual) and the internal lines ([nz][np], FP32
@@ -192,6 +200,44 @@ static cryo_status launch_check(const char *what) {
 // whether a plan's lines share their axial fluxes (see step_body)
 bool step_shared(const cryo_plan *p) { return p->lpw == 1; }
 
+static size_t multi_lds(const cryo_plan *p) {
+    return step_lds(p) + 8 * (size_t)STEP_WAVES * p->np;     // a slot per line (FP32: two planes)
+}
+static int multi_grid(const cryo_plan *p, int K) {
+    const int own = STEP_WAVES - 2 * (K - 1);
+    return (p->nz - 2 + own - 1) / own;
+}
+
+// Steps that one launch takes: on a grid that leaves compute units idle a
+// workgroup steps its neighbours' lines too, as far as it needs them, and
+// saves launches (2.4 us each with the latency of the tables and lines).  As
+// many as leave at most one workgroup per unit; us per step at 1, 2, 3, 4
+// steps, 512 rows (FP64 | FP32):
+//     514 lines   8.2  6.7  6.2  6.0    | 5.3  3.9  3.5  3.3   (4 taken)
+//     1026        8.3  6.9  6.4  11.3   | 5.5  4.1  3.6  5.0   (3)
+//     1538        8.6  7.0  11.7  16.6  | 5.8  4.3  5.1  7.0   (2)
+//     2050        8.9  12.7  11.9  21.9 | 6.2  6.0  5.4  8.8   (1 | 3)
+// FP32 with short chunks fits two workgroups on a unit: three steps gain up to
+// 27 % there (128 rows: 3.9 -> 2.9), 10 rows per lane lose 20 % (7.6 -> 8.7,
+// general laws); two steps at 2050 to 3074 lines gain nothing.
+int step_multi(const cryo_plan *p) {
+    if (!step_shared(p) || p->wpl != 1 || p->rpl > 10 || multi_lds(p) > MAX_STEP_LDS) return 1;
+    for (int K = MULTI_MAX; K > 1; --K)
+        if (multi_grid(p, K) <= N_CU) return K;
+    return p->dtype == CRYO_F32 && p->rpl <= 8 && multi_grid(p, 3) <= 2 * N_CU ? 3 : 1;
+}
+
+// (a value per line where steps share a launch: the mean must not depend on
+// how they are grouped)
+int surf_cols(const cryo_plan *p) { return step_multi(p) > 1 ? p->nz - 2 : step_grid(p); }
+
+// Steps per surface reduction: what fits the memory of SURF_CHUNK rows of one
+// value per workgroup, with values per line an eighth of it (whole launches of
+// 2, 3 or 4 steps).
+int surf_chunk(const cryo_plan *p) {
+    return step_multi(p) > 1 ? SURF_CHUNK / STEP_WAVES / 12 * 12 : SURF_CHUNK;
+}
+
 int step_grid(const cryo_plan *p) {
     const int groups = (p->nz - 2 + p->lpw - 1) / p->lpw;
     const int per_wg = STEP_WAVES / p->wpl;
@@ -300,6 +346,7 @@ static StepArgs<R> step_args(const cryo_plan *p, const void *Tin, void *Tout, do
         a.wz_mid = 1.0 / p->z_full;
         a.wz_end = 0.5 / p->z_full;
     }
+    a.surf_cols = step_multi(p) > 1 ? p->nz - 2 : 0;
     a.groups = step_grid(p);
     a.pulse = p->pulse;
     a.pulse.amplitude *= xs;
@@ -330,9 +377,34 @@ cryo_status launch_step(const cryo_plan *p, const void *Tin, void *Tout, double 
                                 : step_t<float>(p, Tin, Tout, X, partial, flag, s);
 }
 
+template <typename R>
+static cryo_status steps_t(const cryo_plan *p, const void *Tin, void *Tout, int K,
+                           const double *X, double *partial, int *flag, hipStream_t s) {
+    const StepArgs<R> a = step_args<R>(p, Tin, Tout, 0.0, partial, flag);
+    MultiRun<R> run = {};
+    run.K = K;
+    for (int k = 0; k < K; ++k) run.X[k] = (R)(X[k] * (p->eta * p->eta) * a.jsq);
+    const dim3 g(multi_grid(p, K));
+    const int laws = p->poly ? 2 : a.cube ? 0 : 1;
+    const bool built =
+        p->stepped ? MultiLaunch<R, true>::step(laws, p->rpl, g, multi_lds(p), s, a, run)
+                   : MultiLaunch<R, false>::step(laws, p->rpl, g, multi_lds(p), s, a, run);
+    if (!built) return fail(CRYO_ERR_UNSUPPORTED, "radial chunk shape");
+    return launch_check("steps");
+}
+
+// K steps (at most step_multi) in one launch; X: their sources, partial: the
+// first one's partial sums
+cryo_status launch_steps(const cryo_plan *p, const void *Tin, void *Tout, int K, const double *X,
+                         double *partial, int *flag, hipStream_t s) {
+    if (K == 1) return launch_step(p, Tin, Tout, X[0], partial, flag, s);
+    return p->dtype == CRYO_F64 ? steps_t<double>(p, Tin, Tout, K, X, partial, flag, s)
+                                : steps_t<float>(p, Tin, Tout, K, X, partial, flag, s);
+}
+
 cryo_status launch_surf_reduce(const cryo_plan *p, const double *partial, int nsteps,
                                double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_surf_reduce, dim3(nsteps), dim3(WAVE), 0, s, partial, step_grid(p), out);
+    hipLaunchKernelGGL(k_surf_reduce, dim3(nsteps), dim3(WAVE), 0, s, partial, surf_cols(p), out);
     return launch_check("surf_reduce");
 }
 

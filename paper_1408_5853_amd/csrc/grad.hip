@@ -366,7 +366,7 @@ static cryo_status grad_forward(GradRun &r) {
     const size_t F = field_f64(p);
     double *surf = (double *)(w + g.surf);
     double *part = (double *)(w + g.part);
-    const int G = step_grid(p);
+    const int G = surf_cols(p), C = surf_chunk(p);
     // state k: in the stored tail, or one of two buffers (the checkpoints
     // are copies)
     auto state = [&](int64_t k) -> void * {
@@ -384,10 +384,10 @@ static cryo_status grad_forward(GradRun &r) {
                 hipSuccess)
             return fail(CRYO_ERR_DEVICE, "checkpoint copy");
         const double X = p->pulse.amplitude * ln.s;
-        double *pp = ln.obs > 0 ? part + (size_t)((ln.obs - 1) % SURF_CHUNK) * G : nullptr;
+        double *pp = ln.obs > 0 ? part + (size_t)((ln.obs - 1) % C) * G : nullptr;
         st = launch_step(ln.sub ? p->sub : p, cur, nxt, X, pp, flag, s);
         if (st != CRYO_OK) return st;
-        if (ln.obs > 0 && (ln.obs % SURF_CHUNK == 0 || ln.obs == r.N)) {
+        if (ln.obs > 0 && (ln.obs % C == 0 || ln.obs == r.N)) {
             st = launch_surf_reduce(p, part, (int)(ln.obs - done), surf + done, s);
             if (st != CRYO_OK) return st;
             done = ln.obs;

@@ -210,7 +210,7 @@ static void pick_shape(int nr, int *rpl, int *wpl) {
 static int pick_lpw(int nz, int rpl, int wpl, cryo_dtype dtype) {
     if (dtype == CRYO_F32 && rpl <= 10) return 1;
     const int per_wg = STEP_WAVES_HOST / wpl;
-    const double l = (double)(nz - 2) / ((double)per_wg * 256.0);
+    const double l = (double)(nz - 2) / ((double)per_wg * (double)N_CU);
     return std::min(8, std::max(1, (int)std::lround(l)));
 }
 
@@ -675,8 +675,9 @@ cryo_status cryo_init(const cryo_plan *p, void *T, void *stream) {
 }  // extern "C"
 
 // Workspace (and resident state) layout: the error word, the two field
-// buffers of the kernels' internal layout (ping-pong), then the per-workgroup
-// surface partial sums of up to SURF_CHUNK steps.
+// buffers of the kernels' internal layout (ping-pong), then the surface
+// partial sums of surf_chunk steps: per workgroup, or per line where steps
+// share a launch, in the same memory.
 static cryo_status check_ws(const cryo_plan *p, const void *ws, size_t ws_bytes) {
     size_t need = 0;
     cryo_workspace_bytes(p, 0, &need);
@@ -700,31 +701,67 @@ static cryo_status run_steps(const cryo_plan *p, char *w, int *cur_io, int64_t k
     void *buf[2] = {w + 256, w + 256 + field_bytes(p)};
     double *part = (double *)(w + 256 + 2 * field_bytes(p));
     cryo_status st = CRYO_OK;
-    int G = step_grid(p);
+    const int G = surf_cols(p), C = surf_chunk(p), kmax = step_multi(p);
     int64_t done_surf = 0;
     int cur = *cur_io;
-    for (int64_t n = 0; n < nsteps; ++n) {
-        double *pp = surf ? part + (size_t)(n % SURF_CHUNK) * G : nullptr;
-        if (p->sub && pulse_start(p->pulse, k0 + n)) {
+    const auto turn_on = [&](int64_t n) { return p->sub && pulse_start(p->pulse, k0 + n); };
+    // as many steps from n on as one launch may take: up to the turn-on
+    // model's next pulse start and the end of a surface reduction
+    const auto span = [&](int64_t n) {
+        int K = 1;
+        while (K < kmax && n + K < nsteps && (n + K) % C != 0 && !turn_on(n + K)) ++K;
+        return K;
+    };
+    const auto go = [&](const cryo_plan *q, int K, const double *X, double *pp, bool split) {
+        if (split && K > 1) {
+            st = launch_steps(q, buf[cur], buf[cur ^ 1], K - 1, X, pp, flag, s);
+            cur ^= 1;
+            X += K - 1;
+            pp = pp ? pp + (size_t)(K - 1) * G : nullptr;
+            K = 1;
+        }
+        if (st == CRYO_OK) st = launch_steps(q, buf[cur], buf[cur ^ 1], K, X, pp, flag, s);
+        cur ^= 1;
+    };
+    // The result lies where one launch per (sub-)step would have left it (an
+    // even number returns to its buffer, so that a captured call on a resident
+    // state can be replayed): one launch more where that needs it.
+    bool split = false;
+    if (kmax > 1)
+        for (int64_t n = 0; n < nsteps;) {
+            const int K = turn_on(n) ? 1 : span(n);
+            split ^= (K - 1) & 1;
+            n += K;
+        }
+    for (int64_t n = 0; n < nsteps;) {
+        double *pp = surf ? part + (size_t)(n % C) * G : nullptr;
+        if (turn_on(n)) {
             // eq. (22): the pulse's first step as 100 sub-steps of dt / 100
             // (same layout and launch shape; the last one reports the surface)
-            for (int i = 0; i < 100 && st == CRYO_OK; ++i) {
-                double X = p->pulse.amplitude * turn_on_source(p->pulse, k0 + n, i);
-                st = launch_step(p->sub, buf[cur], buf[cur ^ 1], X, i == 99 ? pp : nullptr, flag, s);
-                cur ^= 1;
-            }
+            double X[100];
+            for (int i = 0; i < 100; ++i)
+                X[i] = p->pulse.amplitude * turn_on_source(p->pulse, k0 + n, i);
+            const bool odd = ((99 + kmax - 1) / kmax + 1) & 1;
+            for (int i = 0; i < 99 && st == CRYO_OK; i += kmax)
+                go(p->sub, std::min(kmax, 99 - i), X + i, nullptr, odd && i == 0);
+            if (st == CRYO_OK) go(p->sub, 1, X + 99, pp, false);
+            ++n;
         } else {
-            double X = p->pulse.amplitude * source_fraction(p->pulse, k0 + n);
-            st = launch_step(p, buf[cur], buf[cur ^ 1], X, pp, flag, s);
-            cur ^= 1;
+            const int K = span(n);
+            double X[MULTI_MAX];
+            for (int k = 0; k < K; ++k)
+                X[k] = p->pulse.amplitude * source_fraction(p->pulse, k0 + n + k);
+            go(p, K, X, pp, split);
+            if (K > 1) split = false;
+            n += K;
         }
         if (st != CRYO_OK) return st;
         *cur_io = cur;
-        if (surf && ((n + 1) % SURF_CHUNK == 0 || n + 1 == nsteps)) {
-            int cnt = (int)(n + 1 - done_surf);
+        if (surf && (n % C == 0 || n == nsteps)) {
+            int cnt = (int)(n - done_surf);
             st = launch_surf_reduce(p, part, cnt, surf + done_surf, s);
             if (st != CRYO_OK) return st;
-            done_surf = n + 1;
+            done_surf = n;
         }
     }
     return CRYO_OK;

@@ -16,6 +16,8 @@ constexpr int MAX_LAYERS = 16;
 constexpr int MAX_NR = 2048;
 constexpr int SURF_CHUNK = 1024;    // steps per surface reduction round
 constexpr int STEP_WAVES_HOST = 8;  // waves per stepping workgroup
+constexpr int N_CU = 256;             // compute units of an MI355X
+constexpr int MULTI_MAX = 4;         // steps of one launch (launch_steps), at most
 constexpr int BATCH_LPW = 4;        // default lines per wave of batch instances
 
 // Built chunk shapes (rows per lane, waves per line) of the stepping kernel:
@@ -231,6 +233,11 @@ cryo_status launch_surf_reduce(const cryo_plan *p, const double *partial, int ns
                                double *out, hipStream_t s);
 int step_grid(const cryo_plan *p);
 bool step_shared(const cryo_plan *p);
+int step_multi(const cryo_plan *p);             // steps one launch may take (1: single steps)
+cryo_status launch_steps(const cryo_plan *p, const void *Tin, void *Tout, int K, const double *X,
+                         double *partial, int *flag, hipStream_t s);
+int surf_cols(const cryo_plan *p);              // partial sums of the surface mean per step
+int surf_chunk(const cryo_plan *p);             // steps per reduction of them
 size_t step_lds(const cryo_plan *p);            // dynamic LDS of the stepping kernel
 // what a plan is accepted against: the LDS its shape and domain would take
 // with power tables of either kind (laws may be replaced after the check)

@@ -95,9 +95,17 @@ __device__ inline void each_row(P *base, int lg, F f) {
 // step_march with several lines: 512 x 8194 FP32 18.6 -> 14.1.  16 FP64 rows
 // take 180 registers and 110 KB, one workgroup per unit, and step_march's
 // blocks win there once there are more lines than waves (pick_lpw).
-template <typename R, int RPL, int G, bool CUBE, bool POLY, bool STEPPED>
+//
+// MULTI (one wave per line): K steps in one launch.  A workgroup owns the
+// middle NG - 2 (K - 1) of its lines; the others are its neighbours', stepped
+// here too as long as the owned ones need them (a line less on each side per
+// step), and a line passes from step to step in registers, to its neighbours
+// through an LDS slot.  Groups past either end of the grid hold the z-boundary
+// line (and real lines, discarded).  Owned lines' steps are what single steps
+// give, bit for bit.
+template <typename R, int RPL, int G, bool CUBE, bool POLY, bool STEPPED, bool MULTI>
 __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R *__restrict__ Tin,
-                                 R *__restrict__ Tout, const R X, double *partial) {
+                                   R *__restrict__ Tout, const MultiRun<R> &run, double *partial) {
     constexpr bool PAIR = Pair<R>::on;
     constexpr int NPL = PAIR ? 2 : 1;                 // planes per line (pairs: hi, lo)
     constexpr int NL = WAVE * G;                      // lanes per line
@@ -120,9 +128,12 @@ __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R 
     const LaneWord word = ((const LaneWord *)(a.img + a.lanes))[lg];
     constexpr size_t LS = (size_t)NP * NPL;               // line stride
     constexpr size_t LO = PAIR ? (size_t)NP : 0;          // offset of the low plane
-    const int jf = 1 + blk * NG;                          // the workgroup's first line
-    const bool active = jf + grp < a.nz - 1;
-    const int j = min(jf + grp, a.nz - 2);                // (past the last: run on it, discarded)
+    const int K = MULTI ? run.K : 1;
+    const int jf = 1 + blk * (NG - 2 * (K - 1)) - (K - 1);   // the workgroup's first line
+    const int jr = jf + grp;                              // the group's, or past either end
+    const bool active = jr >= 1 && jr < a.nz - 1 && grp >= K - 1 && grp <= NG - K;
+    // (past the end: on a real line, discarded)
+    const int j = MULTI ? min(max(jr, 0), a.nz - 1) : min(jr, a.nz - 2);
     R *xch = xchg[grp];
     // neighbour rows across the chunk ends (the row itself at the line ends)
     const int qW = lg > 0 ? (RPL - 1) * NL + lg - 1 : 0;
@@ -162,7 +173,7 @@ __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R 
     // step, the lines being slower to arrive than the tables)
     stage_wait();
     load_line(j, Tc, Lc);
-    load_line(j + 1, Tn, Ln);
+    load_line(MULTI ? min(j + 1, a.nz - 1) : j + 1, Tn, Ln);
     {
         const R *b = Tin + (size_t)j * LS;
         TwF = b[qW];
@@ -177,181 +188,226 @@ __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R 
     R Ta[NF], La[NF], Tb[NF], Lb[NF];
 #pragma unroll
     for (int k = 0; k < NF; ++k) {
-        const R *b = Tin + (size_t)(jf - 1) * LS + min(grp + k * NG, RPL - 1) * NL + lg;
+        const R *b = Tin + (size_t)(MULTI ? max(jf - 1, 0) : jf - 1) * LS +
+                     min(grp + k * NG, RPL - 1) * NL + lg;
         Ta[k] = b[0];
         La[k] = PAIR ? b[LO] : (R)0;
         Tb[k] = b[LS];
         Lb[k] = PAIR ? b[LS + LO] : (R)0;
     }
-    // flux into the line from the next one
-    R Fr[RPL];
-    {
-        auto S = law.set((int)word.law);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            if ((a.m.iface >> r) & 1)
-                if ((word.iface >> r) & 1) law.next(S);
-            // every face mean lies between two nodes: one range check per node
-            if constexpr (!PAIR) off = max(off, law.off_range(Tc[r]));
-            Fr[r] = open_face(j, past, r, face(S, Tc[r], Lc[r], Tn[r], Ln[r]));
-            asm volatile("" : "+v"(Fr[r]));              // evaluated here
-            own[r * NL] = Fr[r];
-            if (r & 1) __builtin_amdgcn_sched_barrier(0);   // register pressure
+    R *pass = flux + (NG + 1) * NP;                       // MULTI: a slot per line
+    for (int s = 0; s < K; ++s) {
+        const R X = run.X[s];
+        // an input value is looked at once, by the group that owns its line
+        const bool watch = !MULTI || active || (s == 0 && (jr == 0 || jr == a.nz - 1));
+        if (MULTI && !PAIR && s == 1) {
+            if (a.held[2]) off = max(off, law.off_range(a.val[2]));
+            if (a.held[3]) off = max(off, law.off_range(a.val[3]));
         }
-    }
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-        const int r = grp + k * NG;
-        if (r >= RPL) break;
-        const auto S = law.set((int)word.law + __popc(word.iface & ((2u << r) - 1u)));
-        if constexpr (!PAIR) off = max(off, law.off_range(Ta[k]));
-        flux[r * NL + lg] = open_face(jf - 1, past, r, face(S, Ta[k], La[k], Tb[k], Lb[k]));
-    }
-    if (!PAIR && j + 1 == a.nz - 1) {
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) off = max(off, law.off_range(Tn[r]));
-    }
-    lds_barrier();
-    const size_t base = (size_t)j * LS;
-    const bool up = STEPPED && j > a.z_full;
-    const uint32_t wif = word.iface, wheat = up ? word.heat & ~past : word.heat;
-    // The rows and the forward elimination of each lane's chunk.
-    R a0 = 0, b0 = 1, c0 = 0, d0 = 0;
-    R al[RPL], ga[RPL], de[RPL];
-    {
-        // the outer wall's row (uniform; a terminal line has its own)
-        const int hrow = __builtin_amdgcn_readfirstlane(up ? -1 : a.surf_reg);
-        const uint32_t heat = X != (R)0 ? a.m.heat : 0u;
-        auto S = law.set((int)word.law);
-        // west face of the chunk's first row: east face of the previous row
-        R lamW = law.at(S, TwF + Tc[0]);
-        R dW = dif<R>(TwF, LwF, Tc[0], Lc[0]);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-#pragma clang fp contract(off)                    // both forms round alike
-            const int q = r * NL + lg;
-            const R gw = sgw[q], ge = sge[q];
-            const R Fb = before[r * NL];         // (into the line before, from this one)
-            const R T = Tc[r], Tl = Lc[r];
-            const R Te = (r < RPL - 1) ? Tc[r + 1] : TeL;
-            const R Le = (r < RPL - 1) ? Lc[r + 1] : LeL;
-            // interface rows (eq. (18)): west coefficient the ratio of the
-            // inner to the outer layer's law at the node (the row divided
-            // by the outer law), east one h_i; no other terms
-            const bool some = (a.m.iface >> r) & 1;            // uniform
-            const bool ifc = some && ((wif >> r) & 1);
-            R v = (R)1;
-            if (some)
-                if (ifc) {
-                    v = law.ratio(S, T + T);
-                    law.next(S);
-                }
-            // laws are evaluated from the sum of the two values they average
-            const R lamE = law.at(S, T + Te);
-            R rc = law.template cap<CUBE>(S, T);
-            const R dE = dif<R>(Te, Le, T, Tl);
-            R fw = gw * lamW, fe = ge * lamE, ax = Fr[r] - Fb;
-            if (some)
-                if (ifc) {
-                    fw = gw * v;
-                    fe = ge;
-                    rc = ax = (R)0;
-                }
-            // walls: unit rows with dT = value - T where held
-            if (r == 0 && lg == 0) {
-                fe = ge;
-                rc = a.held[0] ? (R)1 : (R)0;
-                ax = a.held[0] ? dif<R>(a.val[0], (R)0, T, Tl) : (R)0;
-            }
-            if (r == hrow) {
-                asm volatile("" ::: "memory");                  // keeps the branch
-                if (lg == a.surf_lane) {
-                    fw = gw;
-                    rc = a.held[1] ? (R)1 : (R)0;
-                    ax = a.held[1] ? dif<R>(a.val[1], (R)0, T, Tl) : (R)0;
-                }
-            }
-            if constexpr (STEPPED)
-                if (up)
-                    if ((past >> r) & 1) {                     // the terminal's wall, and past it
-                        const bool wall = lg * RPL + r == a.nr_top - 1;
-                        fw = wall ? (R)1 : (R)0;
-                        rc = wall ? (R)0 : (R)1;
-                        fe = ax = (R)0;
-                    }
-            R dd = fma(fe, dE, fw * dW) + ax;
-            if ((heat >> r) & 1) {                             // heater rows
-                const R h = (R)((wheat >> r) & 1);
-                if constexpr (POLY) dd = fma(h, a.joule ? X * rsqrt(T) : X, dd);   // eq. (25)
-                else dd = fma(h, X, dd);
-            }
-            lamW = lamE;
-            dW = -dE;
-            const R aa = -fw, bb = fw + fe + rc, cc = -fe;
-            if (r == 0) {
-                a0 = aa;
-                b0 = bb;
-                c0 = cc;
-                d0 = dd;
-            } else {
-                elim_row<R, RPL>(r, aa, bb, cc, dd, al, ga, de);
-                // eliminate here, not where the results are first used
-                // (the solve): sinking it would keep every row's
-                // coefficients live
-                asm volatile("" : "+v"(al[r]), "+v"(ga[r]), "+v"(de[r]));
-            }
-            // keep the scheduler from hoisting every row's law evaluations
-            // at once (register pressure); rows still overlap pairwise
-            if (RPL >= ROW_FENCE || (r & 1)) __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    R x[RPL];
-    // the line solve is the step's longest dependent chain (the cyclic
-    // reduction's exchanges): a wave inside it issues before a wave still
-    // in its rows, whose independent work fills the gaps (measured: 1 %
-    // on the 1024 x 4096 FP64 step, results bit for bit the same)
-    __builtin_amdgcn_s_setprio(2);
-    solve_tail<R, RPL, G>(a0, b0, c0, d0, al, ga, de, x, lane, wig, xch, STEP_DROP<R>);
-    __builtin_amdgcn_s_setprio(0);
-    // new state: T + dT (pairs: error-free sum, then renormalise)
-    R Hn[RPL], Lnw[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        if constexpr (PAIR) {
-            const R xr = x[r], h = Tc[r];
-            const R s = h + xr;
-            const R bp = s - h;
-            const R err = (h - (s - bp)) + (xr - bp);
-            const R lo = Lc[r] + err;
-            const R h2 = s + lo;
-            Hn[r] = h2;
-            Lnw[r] = lo - (h2 - s);
-        } else {
-            Hn[r] = Tc[r] + x[r];
-            Lnw[r] = (R)0;
-        }
-    }
-    if (active) {
-        each_row<R, RPL, NL>(Tout + base, lg, [&](int r, auto *p) { *p = Hn[r]; });
-        if constexpr (PAIR)
-            each_row<R, RPL, NL>(Tout + base + LO, lg, [&](int r, auto *p) { *p = Lnw[r]; });
-        // z-boundary lines: copied (insulated) or held, after the solve
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-            const bool mine = side == 0 ? j == 1 : j == a.nz - 2;
-            if (!mine) continue;
-            const bool held = a.held[2 + side];
-            // formed here (cold path), not hoisted out of the line loop
-            size_t ob = side == 0 ? (size_t)0 : (size_t)(a.nz - 1) * LS;
-            asm volatile("" : "+v"(ob));
-            R *o = Tout + ob;
+        if (MULTI && s > 0) {
+            // the line after, and the chunk ends; z-boundary lines follow the
+            // line next to them (insulated) or are held
+            const R *mine = pass + grp * NPL * NP, *next = mine + (grp + 1 < NG ? NPL * NP : 0);
+            const bool top = jr == a.nz - 2;
+            const R *src = top ? mine : next;
 #pragma unroll
             for (int r = 0; r < RPL; ++r) {
-                o[r * NL + lg] = held ? a.val[2 + side] : Hn[r];
-                if constexpr (PAIR) o[LO + r * NL + lg] = held ? (R)0 : Lnw[r];
+                Tn[r] = src[r * NL + lg];
+                Ln[r] = PAIR ? src[NP + r * NL + lg] : (R)0;
+            }
+            if (top && a.held[3]) {
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) {
+                    Tn[r] = a.val[3];
+                    Ln[r] = (R)0;
+                }
+            }
+            if (jr == 0) {
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) {
+                    Tc[r] = a.held[2] ? a.val[2] : Tn[r];
+                    Lc[r] = a.held[2] ? (R)0 : Ln[r];
+                }
+            }
+            TwF = mine[qW];
+            TeL = mine[qE];
+            if constexpr (PAIR) {
+                LwF = mine[NP + qW];
+                LeL = mine[NP + qE];
             }
         }
-        if (partial && lg == a.surf_lane) {
+        // flux into the line from the next one
+        R Fr[RPL];
+        {
+            auto S = law.set((int)word.law);
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                if ((a.m.iface >> r) & 1)
+                    if ((word.iface >> r) & 1) law.next(S);
+                // every face mean lies between two nodes: one range check per node
+                if (!PAIR && watch) off = max(off, law.off_range(Tc[r]));
+                Fr[r] = open_face(j, past, r, face(S, Tc[r], Lc[r], Tn[r], Ln[r]));
+                asm volatile("" : "+v"(Fr[r]));              // evaluated here
+                own[r * NL] = Fr[r];
+                if (r & 1) __builtin_amdgcn_sched_barrier(0);   // register pressure
+            }
+        }
+        if (s == 0) {
+#pragma unroll
+            for (int k = 0; k < NF; ++k) {
+                const int r = grp + k * NG;
+                if (r >= RPL) break;
+                const auto S = law.set((int)word.law + __popc(word.iface & ((2u << r) - 1u)));
+                if constexpr (!PAIR && !MULTI) off = max(off, law.off_range(Ta[k]));
+                flux[r * NL + lg] = open_face(jf - 1, past, r, face(S, Ta[k], La[k], Tb[k], Lb[k]));
+            }
+        }
+        if (!PAIR && !MULTI && j + 1 == a.nz - 1) {
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) off = max(off, law.off_range(Tn[r]));
+        }
+        lds_barrier();
+        const size_t base = (size_t)j * LS;
+        const bool up = STEPPED && j > a.z_full;
+        const uint32_t wif = word.iface, wheat = up ? word.heat & ~past : word.heat;
+        // The rows and the forward elimination of each lane's chunk.
+        R a0 = 0, b0 = 1, c0 = 0, d0 = 0;
+        R al[RPL], ga[RPL], de[RPL];
+        {
+            // the outer wall's row (uniform; a terminal line has its own)
+            const int hrow = __builtin_amdgcn_readfirstlane(up ? -1 : a.surf_reg);
+            const uint32_t heat = X != (R)0 ? a.m.heat : 0u;
+            auto S = law.set((int)word.law);
+            // west face of the chunk's first row: east face of the previous row
+            R lamW = law.at(S, TwF + Tc[0]);
+            R dW = dif<R>(TwF, LwF, Tc[0], Lc[0]);
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+#pragma clang fp contract(off)                    // both forms round alike
+                const int q = r * NL + lg;
+                const R gw = sgw[q], ge = sge[q];
+                const R Fb = before[r * NL];         // (into the line before, from this one)
+                const R T = Tc[r], Tl = Lc[r];
+                const R Te = (r < RPL - 1) ? Tc[r + 1] : TeL;
+                const R Le = (r < RPL - 1) ? Lc[r + 1] : LeL;
+                // interface rows (eq. (18)): west coefficient the ratio of the
+                // inner to the outer layer's law at the node (the row divided
+                // by the outer law), east one h_i; no other terms
+                const bool some = (a.m.iface >> r) & 1;            // uniform
+                const bool ifc = some && ((wif >> r) & 1);
+                R v = (R)1;
+                if (some)
+                    if (ifc) {
+                        v = law.ratio(S, T + T);
+                        law.next(S);
+                    }
+                // laws are evaluated from the sum of the two values they average
+                const R lamE = law.at(S, T + Te);
+                R rc = law.template cap<CUBE>(S, T);
+                const R dE = dif<R>(Te, Le, T, Tl);
+                R fw = gw * lamW, fe = ge * lamE, ax = Fr[r] - Fb;
+                if (some)
+                    if (ifc) {
+                        fw = gw * v;
+                        fe = ge;
+                        rc = ax = (R)0;
+                    }
+                // walls: unit rows with dT = value - T where held
+                if (r == 0 && lg == 0) {
+                    fe = ge;
+                    rc = a.held[0] ? (R)1 : (R)0;
+                    ax = a.held[0] ? dif<R>(a.val[0], (R)0, T, Tl) : (R)0;
+                }
+                if (r == hrow) {
+                    asm volatile("" ::: "memory");                  // keeps the branch
+                    if (lg == a.surf_lane) {
+                        fw = gw;
+                        rc = a.held[1] ? (R)1 : (R)0;
+                        ax = a.held[1] ? dif<R>(a.val[1], (R)0, T, Tl) : (R)0;
+                    }
+                }
+                if constexpr (STEPPED)
+                    if (up)
+                        if ((past >> r) & 1) {                     // the terminal's wall, and past it
+                            const bool wall = lg * RPL + r == a.nr_top - 1;
+                            fw = wall ? (R)1 : (R)0;
+                            rc = wall ? (R)0 : (R)1;
+                            fe = ax = (R)0;
+                        }
+                R dd = fma(fe, dE, fw * dW) + ax;
+                if ((heat >> r) & 1) {                             // heater rows
+                    const R h = (R)((wheat >> r) & 1);
+                    if constexpr (POLY) dd = fma(h, a.joule ? X * rsqrt(T) : X, dd);   // eq. (25)
+                    else dd = fma(h, X, dd);
+                }
+                lamW = lamE;
+                dW = -dE;
+                const R aa = -fw, bb = fw + fe + rc, cc = -fe;
+                if (r == 0) {
+                    a0 = aa;
+                    b0 = bb;
+                    c0 = cc;
+                    d0 = dd;
+                } else {
+                    elim_row<R, RPL>(r, aa, bb, cc, dd, al, ga, de);
+                    // eliminate here, not where the results are first used
+                    // (the solve): sinking it would keep every row's
+                    // coefficients live
+                    asm volatile("" : "+v"(al[r]), "+v"(ga[r]), "+v"(de[r]));
+                }
+                // keep the scheduler from hoisting every row's law evaluations
+                // at once (register pressure); rows still overlap pairwise
+                if (RPL >= ROW_FENCE || (r & 1)) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        R x[RPL];
+        // the line solve is the step's longest dependent chain (the cyclic
+        // reduction's exchanges): a wave inside it issues before a wave still
+        // in its rows, whose independent work fills the gaps (measured: 1 %
+        // on the 1024 x 4096 FP64 step, results bit for bit the same)
+        __builtin_amdgcn_s_setprio(2);
+        solve_tail<R, RPL, G>(a0, b0, c0, d0, al, ga, de, x, lane, wig, xch, STEP_DROP<R>);
+        __builtin_amdgcn_s_setprio(0);
+        // new state: T + dT (pairs: error-free sum, then renormalise)
+        R Hn[RPL], Lnw[RPL];
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+            if constexpr (PAIR) {
+                const R xr = x[r], h = Tc[r];
+                const R s = h + xr;
+                const R bp = s - h;
+                const R err = (h - (s - bp)) + (xr - bp);
+                const R lo = Lc[r] + err;
+                const R h2 = s + lo;
+                Hn[r] = h2;
+                Lnw[r] = lo - (h2 - s);
+            } else {
+                Hn[r] = Tc[r] + x[r];
+                Lnw[r] = (R)0;
+            }
+        }
+        if (active && s == K - 1) {
+            each_row<R, RPL, NL>(Tout + base, lg, [&](int r, auto *p) { *p = Hn[r]; });
+            if constexpr (PAIR)
+                each_row<R, RPL, NL>(Tout + base + LO, lg, [&](int r, auto *p) { *p = Lnw[r]; });
+            // z-boundary lines: copied (insulated) or held, after the solve
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const bool mine = side == 0 ? j == 1 : j == a.nz - 2;
+                if (!mine) continue;
+                const bool held = a.held[2 + side];
+                // formed here (cold path), not hoisted out of the line loop
+                size_t ob = side == 0 ? (size_t)0 : (size_t)(a.nz - 1) * LS;
+                asm volatile("" : "+v"(ob));
+                R *o = Tout + ob;
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) {
+                    o[r * NL + lg] = held ? a.val[2 + side] : Hn[r];
+                    if constexpr (PAIR) o[LO + r * NL + lg] = held ? (R)0 : Lnw[r];
+                }
+            }
+        }
+        if (partial && active && lg == a.surf_lane) {
             // the surface row's register is uniform: one scalar test per
             // register, and only the matching register's value is read
             int sreg = __builtin_amdgcn_readfirstlane(a.surf_reg);
@@ -371,12 +427,27 @@ __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R 
                 if (j == 1) sv += a.wz_end * (a.held[2] ? (double)a.val[2] : v);
                 if (j == a.nz - 2) sv += a.wz_end * (a.held[3] ? (double)a.val[3] : v);
             }
+            if (a.surf_cols > 0) {           // a value per line
+                partial[(size_t)s * a.surf_cols + j - 1] = sv;
+                sv = 0.0;
+            }
+        }
+        if (MULTI && s + 1 < K) {
+            R *mine = pass + grp * NPL * NP;
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                Tc[r] = Hn[r];
+                Lc[r] = Lnw[r];
+                mine[r * NL + lg] = Hn[r];
+                if constexpr (PAIR) mine[NP + r * NL + lg] = Lnw[r];
+            }
+            lds_barrier();
         }
     }
     if (__any(off >= POW_HN)) {
         if (lane == 0) atomicOr(a.flag, 2);
     }
-    if (partial) {
+    if (partial && a.surf_cols == 0) {
         if (lane == (a.surf_lane & (WAVE - 1))) wsum[wv] = sv;
         __syncthreads();
         if (t == 0) {
@@ -796,9 +867,17 @@ template <typename R, int RPL, int G, bool CUBE, bool POLY, bool STEPPED, bool S
 __global__ __launch_bounds__(STEP_WAVES *WAVE) void k_step(StepArgs<R> a) {
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     if constexpr (SHARED)
-        step_shared<R, RPL, G, CUBE, POLY, STEPPED>(a, blk, a.Tin, a.Tout, a.X, a.partial);
+        step_shared<R, RPL, G, CUBE, POLY, STEPPED, false>(a, blk, a.Tin, a.Tout, {1, {a.X}},
+                                                           a.partial);
     else
         step_march<R, RPL, G, CUBE, POLY, STEPPED>(a, blk, a.Tin, a.Tout, a.X, a.partial);
+}
+
+// K steps in one launch (step_shared's MULTI)
+template <typename R, int RPL, bool CUBE, bool POLY, bool STEPPED>
+__global__ __launch_bounds__(STEP_WAVES *WAVE) void k_step_multi(StepArgs<R> a, MultiRun<R> run) {
+    step_shared<R, RPL, 1, CUBE, POLY, STEPPED, true>(a, xcd_block(blockIdx.x, gridDim.x), a.Tin,
+                                                      a.Tout, run, a.partial);
 }
 
 // Pulse average over step k (eq. (4)), step units; the host's schedule.
@@ -831,7 +910,7 @@ __global__ __launch_bounds__(STEP_WAVES *WAVE) void k_step_batch(const StepArgs<
     const R *in = a.buf[n & 1];
     R *out = a.buf[(n + 1) & 1];
     if constexpr (SHARED)
-        step_shared<R, RPL, G, CUBE, POLY, STEPPED>(a, m.y, in, out, (R)X, part);
+        step_shared<R, RPL, G, CUBE, POLY, STEPPED, false>(a, m.y, in, out, {1, {(R)X}}, part);
     else
         step_march<R, RPL, G, CUBE, POLY, STEPPED>(a, m.y, in, out, (R)X, part);
 }
@@ -893,6 +972,37 @@ struct StepLaunch {
                                                                                map, n, k0) \
                          : launch_batch_kind<R, true, false, STEPPED, SHARED>(key, g, lds, s, d, \
                                                                               map, n, k0); \
+    }
+
+
+// K-step launches, one wave per line
+template <typename R, bool CUBE, bool POLY, bool STEPPED>
+inline bool launch_multi_kind(int rpl, dim3 g, size_t lds, hipStream_t s, const StepArgs<R> &a,
+                              const MultiRun<R> &run) {
+    switch (rpl) {
+#define MULTI_CASE(RP) \
+    case RP: \
+        hipLaunchKernelGGL((k_step_multi<R, RP, CUBE, POLY, STEPPED>), g, dim3(STEP_WAVES *WAVE), \
+                           lds, s, a, run); \
+        return true;
+        MULTI_CASE(2) MULTI_CASE(3) MULTI_CASE(4) MULTI_CASE(5) MULTI_CASE(6) MULTI_CASE(7)
+        MULTI_CASE(8) MULTI_CASE(10)
+#undef MULTI_CASE
+    }
+    return false;
+}
+template <typename R, bool STEPPED>
+struct MultiLaunch {
+    static bool step(int laws, int rpl, dim3 g, size_t lds, hipStream_t s, const StepArgs<R> &a,
+                     const MultiRun<R> &run);
+};
+#define CRYO_MULTI_LAUNCH(R, STEPPED) \
+    template <> \
+    bool MultiLaunch<R, STEPPED>::step(int laws, int rpl, dim3 g, size_t lds, hipStream_t s, \
+                                       const StepArgs<R> &a, const MultiRun<R> &run) { \
+        return laws == 2 ? launch_multi_kind<R, false, true, STEPPED>(rpl, g, lds, s, a, run) \
+             : laws == 1 ? launch_multi_kind<R, false, false, STEPPED>(rpl, g, lds, s, a, run) \
+                         : launch_multi_kind<R, true, false, STEPPED>(rpl, g, lds, s, a, run); \
     }
 
 }  // namespace cryo
