@@ -114,16 +114,25 @@ __device__ inline double surf_weight(const StepArgs<double> &a, int j) {
     else return a.wz_mid;
 }
 
+// What pass 2 of a step hands to pass 1 of the step before, one line per
+// group: lam^{n+1}, X = T^{n+1} (pass 2's own field), and T^n, whose loads are
+// issued with pass 2's (with the chunk-end neighbours of both).
+template <int RPL>
+struct AdjLine {
+    double lam[RPL], X[RPL], T[RPL];
+    double XwF, XeL, TwF, TeL;
+};
+
 // Pass 1 of one step over this workgroup's line groups (tables staged).
-template <int RPL, int G, bool CUBE, bool STEPPED = false, bool POLY = false>
-// (keep: lam^{n+1} of the group's single line comes in lamR, not from memory)
+// KEEP: one line per group, whose values come in k, not from memory.
+template <int RPL, int G, bool CUBE, bool KEEP, bool STEPPED = false, bool POLY = false>
 // POLY: the interface row's coefficient is the quotient of its inner (slot 2)
 // and outer (slot 3) layer laws, and with the Joule source (eq. (25)) a
 // heater row's source is X sqrt(tref / T) at the old T (a.jsq holds
 // sqrt(tref)).
 __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
                                  const AdjLds<POLY> &tb,
-                                 const double (&lamR)[RPL], bool keep) {
+                                 const AdjLine<RPL> &k) {
     constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
     __shared__ double xchg[NG][9 * G];
     __shared__ double xb[NG][2 * G];
@@ -145,7 +154,7 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
     double gS = 0.0;
 #pragma unroll
     for (int r = 0; r < RPL; ++r) accW[r * WAVE] = accE[r * WAVE] = 0.0;
-    for (int it = 0; it < a.lpw; ++it) {
+    for (int it = 0; it < (KEEP ? 1 : a.lpw); ++it) {
         const int jr = j0 + it;
         const bool active = jr < j1;
         const int j = min(jr, a.nz - 2);
@@ -161,8 +170,8 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
             const int q = r * NL + lg;
-            T[r] = d.T[base + q];
-            MU[r] = keep ? lamR[r] : d.lam_in[base + q];
+            T[r] = KEEP ? k.T[r] : d.T[base + q];
+            MU[r] = KEEP ? k.lam[r] : d.lam_in[base + q];
         }
         // boundary-copy lines feed their sensitivity back to the copied line
         if (j == 1 && !a.held[2]) {
@@ -173,35 +182,47 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
 #pragma unroll
             for (int r = 0; r < RPL; ++r) MU[r] += d.lam_in[(size_t)(a.nz - 1) * LS + r * NL + lg];
         }
-        const double TwF = d.T[base + qW], TeL = d.T[base + qE];
+        const double TwF = KEEP ? k.TwF : d.T[base + qW], TeL = KEEP ? k.TeL : d.T[base + qE];
         // west face of the chunk's first row
         double lamW = law.lawc((sinf[qW] >> 6) & 63, 0.5 * (TwF + T[0]));
         double a0 = 0, b0 = 1, c0 = 0, d0 = 0, ccm2 = 0, bbm1 = 1, ccm1 = 0, mum1 = 0;
         double al[RPL], ga[RPL], de[RPL];
         double aa0 = 0, ccL = 0;
+        // the laws of all rows first, a straight run of code (the row loop
+        // below has a branch per row, across which nothing overlaps)
+        double lamF[RPL], capR[RPL];
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+            const uint32_t inf_r = sinf[r * NL + lg];
+            const double t = T[r], Te = (r < RPL - 1) ? T[r + 1] : TeL;
+            lamF[r] = law.lawc((inf_r >> 6) & 63, 0.5 * (t + Te));
+            if constexpr (CUBE) capR[r] = law.cube((inf_r >> 24) & 63, t);
+            else capR[r] = law.lawc((inf_r >> 24) & 63, t);
+            if (r & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        // (values and table reads are not kept for the last pass: that spilled)
+#pragma unroll
+        for (int r = 0; r < RPL; ++r)
+            asm volatile("" : "+v"(lamF[r]), "+v"(capR[r]) : : "memory");
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
             const int q = r * NL + lg;
             const uint32_t inf_r = sinf[q];
             const uint32_t kind = inf_r & 7;
             const bool cap = kind == K_CAP, ifc = kind == K_IFACE;
-            const double t = T[r], Te = (r < RPL - 1) ? T[r + 1] : TeL;
-            const int le = (inf_r >> 6) & 63, l2 = (inf_r >> 12) & 63;
-            const int lc = (inf_r >> 24) & 63;
-            const double lamE = law.lawc(le, 0.5 * (t + Te));
+            const double t = T[r], lamE = lamF[r];
+            const int l2 = (inf_r >> 12) & 63;
             // rows in the stepping kernel's scaled form: an interface row's
             // west coefficient is the ratio law at the node and its east one
             // h_i; boundary rows have their unit or zero laws folded into gw,
             // ge (slot 2 is the unit law there, the zero law on padding)
             double l2v = l2 == law_unit(a.L) ? 1.0 : 0.0;
-            if (__any(ifc)) {
+            if ((a.m.iface >> r) & 1) {                      // (uniform)
                 double va = law.lawc(l2, t);
                 if constexpr (POLY) va = va / law.lawc((inf_r >> 18) & 63, t);
                 if (ifc) l2v = va;
             }
-            double rc;
-            if constexpr (CUBE) rc = law.cube(lc, t);
-            else rc = law.lawc(lc, t);
+            const double rc = capR[r];
             fw[r] = sgw[q] * (cap ? lamW : l2v);
             fe[r] = sge[q] * (cap ? lamE : 1.0);
             const double aa = -fw[r], bb = fw[r] + fe[r] + rc, cc = -fe[r];
@@ -240,8 +261,8 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
         // T^{n+1} of the line, loaded after the solve (registers)
         double X[RPL];
 #pragma unroll
-        for (int r = 0; r < RPL; ++r) X[r] = d.X[base + r * NL + lg];
-        const double XwF = d.X[base + qW], XeL = d.X[base + qE];
+        for (int r = 0; r < RPL; ++r) X[r] = KEEP ? k.X[r] : d.X[base + r * NL + lg];
+        const double XwF = KEEP ? k.XwF : d.X[base + qW], XeL = KEEP ? k.XeL : d.X[base + qE];
         // radial part of lam^n:  dJ - [y_i dr_i/dT_i + y_{i-1} dr_{i-1}/dT_i + y_{i+1} dr_{i+1}/dT_i]
         // face conductivity derivatives: d(gw lam_W)/dT_i = (1/2) e lam' ... on
         // capacity rows (face-mean argument), e lam / T at interface nodes.
@@ -345,11 +366,11 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
                 lp_prev = lp;
                 // (unconditional: a read under a row test is a branch that
                 // waits for it at once)
-                const double aw = accW[r * WAVE], ae = accE[r * WAVE];
+                const double aw = KEEP ? 0.0 : accW[r * WAVE], ae = KEEP ? 0.0 : accE[r * WAVE];
                 accW[r * WAVE] = cf ? fma(y[r] * fw[r], Dw, aw) : aw;
                 accE[r * WAVE] = cf ? fma(y[r] * fe[r], De, ae) : ae;
                 gS += ((inf_r >> 3) & 1) ? (POLY ? y[r] * chi : y[r]) : 0.0;
-                __builtin_amdgcn_sched_barrier(0);
+                if (r & 1) __builtin_amdgcn_sched_barrier(0);
             }
             d.lpart[base + (RPL - 1) * NL + lg] = lp_prev - qwNext;
         }
@@ -360,8 +381,10 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
     __shared__ double gsum[ADJ_WAVES];
     if (lane == 0) gsum[wv] = v;
     __syncthreads();
-    // this workgroup's running sums (one slot per workgroup: no other writer),
-    // its line groups added in a fixed order
+    // this workgroup's running sums (one slot per workgroup: no other writer,
+    // the order is fixed; an atomic add only spares waiting for the old value,
+    // about 2k cycles at each of the kernel's three sums), its line groups
+    // added in a fixed order
     const double *accL = tb.sums;
     double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np;
     for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
@@ -372,14 +395,14 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
             sw += accL[o];
             se += accL[(size_t)ADJ_WAVES * RPL * WAVE + o];
         }
-        acc[q] += sw;
-        acc[a.np + q] += se;
+        unsafeAtomicAdd(acc + q, sw);
+        unsafeAtomicAdd(acc + a.np + q, se);
     }
     if (threadIdx.x == 0) {
         double tot = 0.0;
         for (int w = 0; w < ADJ_WAVES; ++w) tot += gsum[w];
-        d.accg[2 * blockIdx.x] += tot * d.xs * d.s;
-        d.accg[2 * blockIdx.x + 1] += tot * a.pulse.amplitude * d.ds;
+        unsafeAtomicAdd(d.accg + 2 * blockIdx.x, tot * d.xs * d.s);
+        unsafeAtomicAdd(d.accg + 2 * blockIdx.x + 1, tot * a.pulse.amplitude * d.ds);
     }
 }
 
@@ -387,19 +410,35 @@ template <int RPL, int G, bool CUBE, bool STEPPED, bool POLY = false>
 __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj1(StepArgs<double> a, AdjArgs d) {
     extern __shared__ __align__(16) unsigned char smem[];
     const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem);
-    const double none[RPL] = {};
-    adj1_body<RPL, G, CUBE, STEPPED, POLY>(a, d, tb, none, false);
+    const AdjLine<RPL> none = {};
+    adj1_body<RPL, G, CUBE, false, STEPPED, POLY>(a, d, tb, none);
+}
+
+// A workgroup's axial row sums: its line groups added in a fixed order.
+template <int RPL, int G>
+__device__ inline void adj2_sums(const StepArgs<double> &a, const AdjArgs &d, double *sums,
+                                 const double (&accZ)[RPL]) {
+    constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) sums[(size_t)wv * RPL * WAVE + r * WAVE + lane] = accZ[r];
+    __syncthreads();
+    double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np + 2 * a.np;
+    for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
+        const int r = q / NL, lq = q % NL, w0 = lq / WAVE, ln = lq % WAVE;
+        double sz = 0.0;
+        for (int g = 0; g < NG; ++g)
+            sz += sums[(size_t)(g * G + w0) * RPL * WAVE + (size_t)r * WAVE + ln];
+        unsafeAtomicAdd(acc + q, sz);
+    }
 }
 
 // Pass 2: axial faces.  Each interior line j adds the terms of its two
 // axial faces (capacity rows), and the lines next to the z-boundaries write
 // the boundary lines' lam^n.
 template <int RPL, int G, bool STEPPED = false, bool POLY = false>
-// (keep: lam^n of the group's single line goes to lamR, not to memory; the
-// boundary lines' lam^n is always written)
 __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
-                                 const AdjLds<POLY> &tb,
-                                 double (&lamR)[RPL], bool keep) {
+                                 const AdjLds<POLY> &tb) {
     constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
     const uint32_t *sinf = tb.sinf;                      // this line's table
     const auto &law = tb.law;
@@ -490,8 +529,7 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
                 if (!STEPPED && lg == a.surf_lane && r == a.surf_reg) le_ += cS * a.wz_end;
                 d.lam_out[(size_t)(a.nz - 1) * LS + q] = le_;
             }
-            if (keep) lamR[r] = lam;
-            else d.lam_out[base + q] = lam;
+            d.lam_out[base + q] = lam;
             // one row at a time (register pressure)
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -502,29 +540,113 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
             Tc[r] = Tn[r];
         }
     }
-    // this workgroup's sums, its line groups added in a fixed order
-    double *accL = tb.sums;
+    adj2_sums<RPL, G>(a, d, tb.sums, accZ);
+}
+
+// Pass 2 of a group's single line: both faces of a row at once (two law
+// evaluations side by side, nothing carried between rows).  lam^n goes to
+// k, the boundary lines' to memory; T1: the field of the step before.
+template <int RPL, int G, bool STEPPED, bool POLY>
+__device__ inline void adj2_line(const StepArgs<double> &a, const AdjArgs &d,
+                                 const AdjLds<POLY> &tb, const double *T1, AdjLine<RPL> &k) {
+    constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
+    const auto &law = tb.law;
+    const int lane = threadIdx.x & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int grp = wv / G, wig = wv % G, lg = wig * WAVE + lane;
+    const int jr = 1 + blockIdx.x * NG + grp;
+    const bool active = jr < a.nz - 1;
+    const int j = min(jr, a.nz - 2);                         // (past the last: discarded)
+    const size_t LS = a.np, base = (size_t)j * LS;
+    const uint32_t *sinf = STEPPED && j > a.z_full ? tb.sinf2 : tb.sinf;
+    const double cS = d.cS ? *d.cS : 0.0;                    // dJ/dS of this state
+    double T[RPL], Ts[RPL], Tn[RPL], Y[RPL], Ys[RPL], Yn[RPL], LP[RPL], accZ[RPL];
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) accL[(size_t)wv * RPL * WAVE + r * WAVE + lane] = accZ[r];
-    __syncthreads();
-    double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np + 2 * a.np;
-    for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
-        const int r = q / NL, lq = q % NL, w0 = lq / WAVE, ln = lq % WAVE;
-        double sz = 0.0;
-        for (int g = 0; g < NG; ++g)
-            sz += accL[(size_t)(g * G + w0) * RPL * WAVE + (size_t)r * WAVE + ln];
-        acc[q] += sz;
+    for (int r = 0; r < RPL; ++r) {
+        const int q = r * NL + lg;
+        T[r] = d.T[base + q];
+        Ts[r] = d.T[base - LS + q];
+        Tn[r] = d.T[base + LS + q];
     }
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        const int q = r * NL + lg;
+        Y[r] = d.Y[base + q];
+        Ys[r] = j > 1 ? d.Y[base - LS + q] : 0.0;
+        Yn[r] = j < a.nz - 2 ? d.Y[base + LS + q] : 0.0;
+        LP[r] = d.lpart[base + q];
+    }
+    {
+        const int qW = lg > 0 ? (RPL - 1) * NL + lg - 1 : 0;
+        const int qE = lg < NL - 1 ? lg + 1 : (RPL - 1) * NL + lg;
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+            k.X[r] = T[r];
+            k.T[r] = T1[base + r * NL + lg];
+        }
+        k.TwF = T1[base + qW];
+        k.TeL = T1[base + qE];
+        k.XwF = d.T[base + qW];
+        k.XeL = d.T[base + qE];
+    }
+    const bool low = active && j == 1, high = active && j == a.nz - 2;
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+        const int q = r * NL + lg;
+        const uint32_t inf_r = sinf[q];
+        const bool cap = (inf_r & 7) == K_CAP;
+        bool capn = cap;
+        // the step face (eq. (9)): closed where the terminal's row above is
+        // not a capacity row
+        if constexpr (STEPPED)
+            if (j == a.z_full && (tb.sinf2[q] & 7) != K_CAP) capn = false;
+        // non-capacity rows take the zero law: every face term vanishes
+        const int id = (inf_r >> 12) & 63, lzs = cap ? id : law_zero(a.L);
+        const int lzn = capn ? id : law_zero(a.L);
+        const double t = T[r], fs = 0.5 * (t + Ts[r]), fn = 0.5 * (t + Tn[r]);
+        const double ds = t - Ts[r], dn = Tn[r] - t;
+        const double ls = law.lawc(lzs, fs), ln = law.lawc(lzn, fn);
+        double gs, gn;
+        if constexpr (POLY) {
+            gs = 0.5 * poly_dlaw(law, lzs, fs);
+            gn = 0.5 * poly_dlaw(law, lzn, fn);
+        } else {
+            gs = 0.5 * law.expo(lzs) * ls * rcp(fs);
+            gn = 0.5 * law.expo(lzn) * ln * rcp(fn);
+        }
+        const double y = Y[r];
+        // (gn dn - ln: d F_N / d T_j; gs ds + ls: d F_S / d T_j)
+        k.lam[r] = LP[r] + (gn * dn - ln) * (y - Yn[r]) + (gs * ds + ls) * (Ys[r] - y);
+        accZ[r] = active ? y * (ln * dn - ls * ds) : 0.0;
+        if (low) {
+            double l0 = (gs * ds - ls) * (0.0 - y);          // d F_S / d T_0
+            if (lg == a.surf_lane && r == a.surf_reg) l0 += cS * a.wz_end;
+            d.lam_out[q] = l0;
+        }
+        if (high) {
+            double l1 = (gn * dn + ln) * (y - 0.0);          // d F_N / d T_{nz-1}
+            // (on a stepped domain the top line is not on the surface)
+            if (!STEPPED && lg == a.surf_lane && r == a.surf_reg) l1 += cS * a.wz_end;
+            d.lam_out[(size_t)(a.nz - 1) * LS + q] = l1;
+        }
+        if (r & 1) __builtin_amdgcn_sched_barrier(0);        // register pressure
+    }
+    adj2_sums<RPL, G>(a, d, tb.sums, accZ);
 }
 
 template <int RPL, int G, bool STEPPED, bool POLY = false>
 __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj2(StepArgs<double> a, AdjArgs d) {
     extern __shared__ __align__(16) unsigned char smem[];
     const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem);
-    double lamR[RPL];
-    adj2_body<RPL, G, STEPPED, POLY>(a, d, tb, lamR, false);
+    adj2_body<RPL, G, STEPPED, POLY>(a, d, tb);
 }
 
+// Bound by a workgroup's chain: 42k cycles on 512 x 2048 with two waves per
+// SIMD (loads of the three lines 5k, axial rows 6k, its sums 4.6k, radial rows
+// 5k, solve 2k, last pass 6k, sums 4.4k), 17 of its 21 us also on a grid of a
+// quarter the lines.  26.5 us a step before the sums were atomic adds, both
+// faces of a row one pass and the field passed on in registers; the laws of a
+// line as a loop of their own before its rows took the general-law kernels
+// from 248 spilled bytes per lane to none.
 // Pass 2 of step k and pass 1 of step k - 1 in one launch: each line group
 // finishes lam^k of its lines (in registers for one line per group, else
 // written to memory and read back by the same lanes), then runs the next
@@ -536,12 +658,13 @@ __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj21(StepArgs<double> a, A
                                                            AdjArgs d1) {
     extern __shared__ __align__(16) unsigned char smem[];
     const AdjLds<POLY> tb = adj_stage<STEPPED, POLY>(a, smem);
-    // one line per group: lam^k stays in registers between the phases (no
-    // other group reads it)
-    double lamR[RPL] = {};
-    adj2_body<RPL, G, STEPPED, POLY>(a, d2, tb, lamR, KEEP);
+    // one line per group: lam^k and T^k stay in registers between the phases
+    // (no other group reads that lam^k); T^{k-1} is loaded behind the first
+    AdjLine<RPL> k = {};
+    if constexpr (KEEP) adj2_line<RPL, G, STEPPED, POLY>(a, d2, tb, d1.T, k);
+    else adj2_body<RPL, G, STEPPED, POLY>(a, d2, tb);
     __syncthreads();           // the LDS row sums area passes to the next phase
-    adj1_body<RPL, G, CUBE, STEPPED, POLY>(a, d1, tb, lamR, KEEP);
+    adj1_body<RPL, G, CUBE, KEEP, STEPPED, POLY>(a, d1, tb, k);
 }
 
 // lam^N = dJ_N / dT^N: the surface weights on the outer row
@@ -629,7 +752,8 @@ cryo_status launch_adj(const cryo_plan *p, int pass, const AdjArgs &d, int *flag
     const size_t lds = adj_lds(p);
     const int key = p->rpl * 10 + p->wpl;
     if (pass == 21 && !d1) return fail(CRYO_ERR_ARG, "fused adjoint passes need two steps");
-    const bool cube = a.cube, keep = a.lpw == 1;
+    // (one line per group: the passes share the field between their steps)
+    const bool cube = a.cube, keep = a.lpw == 1 && pass == 21 && d1->X == d.T;
 #define ADJ_CASE(R_, G_)                                                                    \
     case R_ * 10 + G_:                                                                      \
         if (p->poly && p->stepped)                                                          \
