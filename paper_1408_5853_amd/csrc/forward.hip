@@ -197,7 +197,7 @@ static cryo_status launch_check(const char *what) {
     return CRYO_OK;
 }
 
-// whether a plan's lines share their axial fluxes (see step_body)
+// whether a plan's lines share their axial fluxes (see step_shared in step_kernel.h)
 bool step_shared(const cryo_plan *p) { return p->lpw == 1; }
 
 static size_t multi_lds(const cryo_plan *p) {
