@@ -163,6 +163,30 @@ static cryo_status batch_build_buckets(cryo_batch *b) {
 
 using namespace cryo;
 
+// Default lines per wave of a batch.  Where the instances fill the device
+// together, longer line blocks amortise each block's start-up line
+// (BATCH_LPW); a batch of few lines takes shorter blocks, down to one line,
+// since its launches are one block's latency each: the longest blocks that
+// still give 8 workgroups per compute unit.  us for 40 steps at 4 lines, at
+// the choice for 1, 4 and 8 workgroups per unit, and at 1 line (cells of 128 x
+// 256 to 512 x 2048):
+//     9 mixed laws FP64  3993  3980  2159  2118  2151
+//     9 FP64             2729  2740  1844  1797  1791
+//     24 FP64            3964  3984  3828  3401  3398
+//     64 FP64            9168  9176  9217  9180  9072
+//     160 FP32 pairs    11675 11850 11775 11791 12580
+static int batch_lpw(const std::vector<cryo_plan *> &plans) {
+    for (int lpw = BATCH_LPW; lpw > 1; lpw /= 2) {
+        int64_t wg = 0;
+        for (const cryo_plan *p : plans) {
+            const int per_wg = lpw * (STEP_WAVES_HOST / p->wpl);
+            wg += (p->nz - 2 + per_wg - 1) / per_wg;
+        }
+        if (wg >= 8 * N_CU) return lpw;
+    }
+    return 1;
+}
+
 extern "C" {
 
 cryo_status cryo_batch_create(int32_t n, const cryo_problem *probs, cryo_dtype dtype,
@@ -198,10 +222,6 @@ cryo_status cryo_batch_create_with(int32_t n, const cryo_problem *probs, cryo_dt
         }
         if (st == CRYO_OK && shapes)
             st = cryo_plan_set_shape(p, shapes[3 * i], shapes[3 * i + 1], shapes[3 * i + 2]);
-        else if (st == CRYO_OK)
-            // the instances fill the device together: longer line blocks
-            // amortise each block's start-up line
-            st = cryo_plan_set_shape(p, p->rpl, p->wpl, std::min(BATCH_LPW, p->nz - 2));
         if (st != CRYO_OK) {
             std::string m = "instance " + std::to_string(i) + ": " + cryo_last_error();
             if (p) cryo_plan_destroy(p);
@@ -209,6 +229,17 @@ cryo_status cryo_batch_create_with(int32_t n, const cryo_problem *probs, cryo_dt
             return fail(st, m);
         }
         b->plans.push_back(p);
+    }
+    if (!shapes) {
+        const int lpw = batch_lpw(b->plans);
+        for (cryo_plan *p : b->plans) {
+            const cryo_status st =
+                cryo_plan_set_shape(p, p->rpl, p->wpl, std::min(lpw, p->nz - 2));
+            if (st != CRYO_OK) {
+                cryo_batch_destroy(b);
+                return st;
+            }
+        }
     }
     b->off.assign(n + 1, 0);
     for (int i = 0; i < n; ++i) b->off[i + 1] = b->off[i] + abi_elems(b->plans[i]);
