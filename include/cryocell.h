@@ -440,7 +440,7 @@ cryo_status cryo_gradient_many(int32_t n, cryo_plan *const *plans, const void *c
 
 /* Create a batch of n instances.  `shapes` (nullable) gives per instance
  * (rows_per_lane, waves_per_line, lines_per_wave), e.g. from cryo_autotune;
- * otherwise each plan's default chunk shape with 4 lines per wave.  Errors
+ * otherwise each plan's default chunk shape with 1, 2 or 4 lines per wave.  Errors
  * name the failing instance. */
 cryo_status cryo_batch_create(int32_t n, const cryo_problem *probs, cryo_dtype dtype,
                               const int32_t *shapes, cryo_batch **out);
