@@ -314,7 +314,7 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
         for (int i = 0; i < n; ++i) {
             const cryo_plan *p = b->plans[i];
             char *f = w + b->ws_field[i];
-            conv[i] = BatchConv{b->off[i], {f, f + field_bytes_internal(p)}, p->prob.T_init,
+            conv[i] = BatchConv{b->off[i], {f, f + field_bytes_internal(p)}, pad_value(p),
                                 p->nz, p->nr, p->np, p->rpl, WAVE * p->wpl, (int *)w + i};
         }
         hipError_t e = hipMemcpy(b->d_block, b->h_block.data(), b->block_bytes,

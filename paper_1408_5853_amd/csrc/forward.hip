@@ -247,7 +247,7 @@ int step_grid(const cryo_plan *p) {
 template <typename R>
 static ConvArgs<R> conv_args(const cryo_plan *p, const void *T, const void *Ti, int *flag) {
     return ConvArgs<R>{(R *)T, (R *)Ti, p->nz, p->nr, p->np, p->rpl, WAVE * p->wpl,
-                       (R)p->prob.T_init, flag};
+                       (R)pad_value(p), flag};
 }
 template <typename R>
 static void launch_convert(const cryo_plan *p, bool in, const void *T, const void *Ti, int *flag,

@@ -315,12 +315,29 @@ static void fill_rows(cryo_plan *p, int n, bool terminal, double *fgwo, double *
     }
 }
 
+// The value of a field's padding rows: one where the outer layer's laws are
+// positive and finite in either type, whatever T_init and the field: the power
+// laws' reference temperature (their values there are k0 and c0), the coldest
+// prescribed temperature under polynomial laws (checked there); on the law
+// tables' range.
+double pad_value(const cryo_plan *p) {
+    double T = p->layers.back().mat.tref;
+    if (p->poly) {
+        T = p->prob.T_init;
+        for (int s = 0; s < 4; ++s)
+            if (p->prob.bc.kind[s] == CRYO_HELD) T = std::min(T, p->prob.bc.value[s]);
+    }
+    return std::min(std::max(T, POW_TLO), 0.5 * POW_THI);
+}
+
 static void build_row_tables(cryo_plan *p) {
     const int nr = p->nr, L = p->L, np = p->np, nl = np / p->rpl;
     const int ZERO = law_zero(L), UNIT = law_unit(L);
     // Padding past the line: capacity rows of the outer layer with no radial
-    // coupling (gw = ge = 0), so that they need no treatment of their own;
-    // nothing reads them.  polynomial laws divide slot 2 by slot 3 (unit).
+    // coupling (gw = ge = 0), whose values no step changes (see own_rows), so
+    // that the kernels need no case for them.  The outer wall's and the first
+    // padding row's face laws meet a zero factor: pad_value keeps them finite.
+    // Polynomial laws divide slot 2 by slot 3 (unit).
     const uint32_t last = p->lay[nr - 1], one = p->poly ? UNIT : ZERO;
     p->fgw.assign(np, 0.0);
     p->fge.assign(np, 0.0);

@@ -220,6 +220,7 @@ double source_fraction(const Pulse &p, int64_t k);
 bool pulse_starts_on_steps(const Pulse &p);
 bool pulse_start(const Pulse &p, int64_t k);
 double turn_on_source(const Pulse &p, int64_t k, int i);
+double pad_value(const cryo_plan *p);           // of the rows past a line
 
 // launchers (forward.hip)
 cryo_status launch_to_internal(const cryo_plan *p, const void *T, void *Ti, int *flag,

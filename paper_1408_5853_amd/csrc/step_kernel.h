@@ -61,6 +61,21 @@ __device__ inline void each_row(P *base, int lg, F f) {
     }
 }
 
+// Rows of this lane's chunk that belong to the line (nodes 0..nr-1); the rest is
+// padding.  A step leaves padding rows as they are: they have no radial
+// coupling, and every line's hold the same value (pad_value), so no axial flux
+// either.  That holds for the z-boundary lines too, which is why a held value
+// is written to the line's own rows only.  (Formed where it is used, a cold
+// path, from the lane's number anew: hoisted out of it the comparisons take a
+// register pair per row, and a lane number kept for it a register.)
+template <typename R, int RPL>
+__device__ inline int own_rows(const StepArgs<R> &a, int wig) {
+    unsigned all = ~0u;
+    asm volatile("" : "+s"(all));
+    const int lane = __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+    return (a.surf_lane - wig * WAVE - lane) * RPL + a.surf_reg + 1;
+}
+
 // One step of eq. (8).  A line is spread over G waves (NL = 64 G lanes, each
 // lane a chunk of RPL rows); a workgroup of STEP_WAVES waves runs NG =
 // STEP_WAVES / G lines side by side.  Two forms: one line per line group
@@ -215,18 +230,21 @@ __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R 
                 Tn[r] = src[r * NL + lg];
                 Ln[r] = PAIR ? src[NP + r * NL + lg] : (R)0;
             }
+            // (a held value goes to the line's own rows, as below)
             if (top && a.held[3]) {
+                const int n = own_rows<R, RPL>(a, wig);
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
-                    Tn[r] = a.val[3];
-                    Ln[r] = (R)0;
+                    Tn[r] = r < n ? a.val[3] : Tn[r];
+                    Ln[r] = r < n ? (R)0 : Ln[r];
                 }
             }
             if (jr == 0) {
+                const int n = a.held[2] ? own_rows<R, RPL>(a, wig) : 0;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
-                    Tc[r] = a.held[2] ? a.val[2] : Tn[r];
-                    Lc[r] = a.held[2] ? (R)0 : Ln[r];
+                    Tc[r] = r < n ? a.val[2] : Tn[r];
+                    Lc[r] = r < n ? (R)0 : Ln[r];
                 }
             }
             TwF = mine[qW];
@@ -395,15 +413,16 @@ __device__ inline void step_shared(const StepArgs<R> &a, const int blk, const R 
             for (int side = 0; side < 2; ++side) {
                 const bool mine = side == 0 ? j == 1 : j == a.nz - 2;
                 if (!mine) continue;
-                const bool held = a.held[2 + side];
+                // (held: the line's own rows, see own_rows)
+                const int n = a.held[2 + side] ? own_rows<R, RPL>(a, wig) : 0;
                 // formed here (cold path), not hoisted out of the line loop
                 size_t ob = side == 0 ? (size_t)0 : (size_t)(a.nz - 1) * LS;
                 asm volatile("" : "+v"(ob));
                 R *o = Tout + ob;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
-                    o[r * NL + lg] = held ? a.val[2 + side] : Hn[r];
-                    if constexpr (PAIR) o[LO + r * NL + lg] = held ? (R)0 : Lnw[r];
+                    o[r * NL + lg] = r < n ? a.val[2 + side] : Hn[r];
+                    if constexpr (PAIR) o[LO + r * NL + lg] = r < n ? (R)0 : Lnw[r];
                 }
             }
         }
@@ -790,15 +809,16 @@ __device__ inline void step_march(const StepArgs<R> &a, const int blk, const R *
             for (int side = 0; side < 2; ++side) {
                 const bool mine = side == 0 ? j == 1 : j == a.nz - 2;
                 if (!mine) continue;
-                const bool held = a.held[2 + side];
+                // (held: the line's own rows, see own_rows)
+                const int n = a.held[2 + side] ? own_rows<R, RPL>(a, wig) : 0;
                 // formed here (cold path), not hoisted out of the line loop
                 size_t ob = side == 0 ? (size_t)0 : (size_t)(a.nz - 1) * LS;
                 asm volatile("" : "+v"(ob));
                 R *o = Tout + ob;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
-                    o[r * NL + lg] = held ? a.val[2 + side] : Hn[r];
-                    if constexpr (PAIR) o[LO + r * NL + lg] = held ? (R)0 : Lnw[r];
+                    o[r * NL + lg] = r < n ? a.val[2 + side] : Hn[r];
+                    if constexpr (PAIR) o[LO + r * NL + lg] = r < n ? (R)0 : Lnw[r];
                 }
             }
             if (partial && lg == a.surf_lane) {
