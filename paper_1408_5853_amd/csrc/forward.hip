@@ -231,17 +231,28 @@ int step_multi(const cryo_plan *p) {
 // how they are grouped)
 int surf_cols(const cryo_plan *p) { return step_multi(p) > 1 ? p->nz - 2 : step_grid(p); }
 
-// Steps per surface reduction: what fits the memory of SURF_CHUNK rows of one
-// value per workgroup, with values per line an eighth of it (whole launches of
-// 2, 3 or 4 steps).
-int surf_chunk(const cryo_plan *p) {
-    return step_multi(p) > 1 ? SURF_CHUNK / STEP_WAVES / 12 * 12 : SURF_CHUNK;
-}
-
-int step_grid(const cryo_plan *p) {
-    const int groups = (p->nz - 2 + p->lpw - 1) / p->lpw;
+static int grid_of(const cryo_plan *p, int lpw) {
+    const int groups = (p->nz - 2 + lpw - 1) / lpw;
     const int per_wg = STEP_WAVES / p->wpl;
     return (groups + per_wg - 1) / per_wg;
+}
+int step_grid(const cryo_plan *p) { return grid_of(p, p->lpw); }
+
+// FP32 pairs at their default of one line per wave run up to 8 workgroups per
+// compute unit; their sums take the memory of the balanced grid's, so that a
+// large grid's workspace (and what fits cryo_forward_noalloc's array) does not
+// grow by a second part: 512 x 8194 66.0 MiB, 72.0 with all workgroups' sums.
+int surf_grid(const cryo_plan *p) {
+    const bool one = one_line_shape(p->dtype, p->rpl) && p->lpw == 1;
+    return grid_of(p, one ? balanced_lpw(p->nz, p->wpl) : p->lpw);
+}
+
+// Steps per surface reduction: what fits the memory of SURF_CHUNK rows of one
+// value per workgroup of surf_grid; with values per line an eighth of it (whole
+// launches of 2, 3 or 4 steps).
+int surf_chunk(const cryo_plan *p) {
+    const int c = (int)std::min<int64_t>((int64_t)SURF_CHUNK * surf_grid(p) / surf_cols(p), SURF_CHUNK);
+    return step_multi(p) > 1 ? std::min(c, SURF_CHUNK / STEP_WAVES) / 12 * 12 : c;
 }
 
 template <typename R>

@@ -119,7 +119,7 @@ static GradLayout grad_layout_store(const cryo_plan *p, int64_t N, int64_t ckpt,
     g.flag = o; o += 256;
     g.fwd_buf[0] = o; o += F;
     g.fwd_buf[1] = o; o += F;
-    g.part = o; o += al256(sizeof(double) * (size_t)SURF_CHUNK * step_grid(p));
+    g.part = o; o += al256(sizeof(double) * (size_t)SURF_CHUNK * surf_grid(p));
     g.ck = o; o += F * (size_t)g.nck;
     // segment states a+1 .. b (state a is read from its checkpoint)
     g.seg = o; o += g.H > 0 ? F * (size_t)K : 0;

@@ -199,19 +199,23 @@ static void pick_shape(int nr, int *rpl, int *wpl) {
     *wpl = w;
 }
 
+// Lines per wave for about one workgroup per compute unit of an MI355X (256).
+int balanced_lpw(int nz, int wpl) {
+    const int per_wg = STEP_WAVES_HOST / wpl;
+    const double l = (double)(nz - 2) / ((double)per_wg * (double)N_CU);
+    return std::min(8, std::max(1, (int)std::lround(l)));
+}
+
 // Lines per wave.  FP32 pairs: one (step_shared; two or more workgroups share
 // a compute unit and take turns with memory and arithmetic) up to 10 rows per
 // lane, on any grid: 512 x 4098 9.1 us a step against 10.2 with 2 lines, 512 x
 // 8194 14.2 against 16.6 and 18.6 (2, 4 lines), 640 x 4098 11.6 against 11.4.
-// Otherwise about one workgroup per compute unit of an MI355X (256), so that
-// every unit works and each line group amortises its start-up line: FP64 512
-// x 4098 14.3, 14.1, 21.4 us (1, 2, 4 lines), 640 x 4098 18.7, 17.0, 26.2,
-// 1024 x 4096 29.1, 23.9, 41; FP32 1024 x 4096 16.9, 16.5, 28.
+// Otherwise balanced over the units, so that every unit works and each line
+// group amortises its start-up line: FP64 512 x 4098 14.3, 14.1, 21.4 us (1, 2,
+// 4 lines), 640 x 4098 18.7, 17.0, 26.2, 1024 x 4096 29.1, 23.9, 41; FP32 1024
+// x 4096 16.9, 16.5, 28.
 static int pick_lpw(int nz, int rpl, int wpl, cryo_dtype dtype) {
-    if (dtype == CRYO_F32 && rpl <= 10) return 1;
-    const int per_wg = STEP_WAVES_HOST / wpl;
-    const double l = (double)(nz - 2) / ((double)per_wg * (double)N_CU);
-    return std::min(8, std::max(1, (int)std::lround(l)));
+    return one_line_shape(dtype, rpl) ? 1 : balanced_lpw(nz, wpl);
 }
 
 // The device's table image, made once on the first call that needs the device
@@ -679,7 +683,7 @@ static size_t field_bytes(const cryo_plan *p) {
 
 cryo_status cryo_workspace_bytes(const cryo_plan *p, int64_t nsteps, size_t *bytes) {
     if (!p || !bytes || nsteps < 0) return fail(CRYO_ERR_ARG, "bad argument");
-    size_t part = sizeof(double) * (size_t)SURF_CHUNK * step_grid(p);
+    size_t part = sizeof(double) * (size_t)SURF_CHUNK * surf_grid(p);
     *bytes = 256 + 2 * field_bytes(p) + ((part + 255) & ~(size_t)255);
     return CRYO_OK;
 }
@@ -694,7 +698,7 @@ cryo_status cryo_init(const cryo_plan *p, void *T, void *stream) {
 // Workspace (and resident state) layout: the error word, the two field
 // buffers of the kernels' internal layout (ping-pong), then the surface
 // partial sums of surf_chunk steps: per workgroup, or per line where steps
-// share a launch, in the same memory.
+// share a launch, in the memory of SURF_CHUNK steps of surf_grid workgroups.
 static cryo_status check_ws(const cryo_plan *p, const void *ws, size_t ws_bytes) {
     size_t need = 0;
     cryo_workspace_bytes(p, 0, &need);

@@ -27,6 +27,9 @@ constexpr int BATCH_LPW = 4;        // default lines per wave of batch instances
     X(2, 1) X(3, 1) X(4, 1) X(5, 1) X(6, 1) X(7, 1) X(8, 1) X(10, 1) X(12, 1) X(16, 1) \
     X(4, 2) X(8, 2) X(4, 4) X(8, 4)
 constexpr int ONE_WAVE_RPL[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 16};
+// FP32 pairs that take one line per wave by default (pick_lpw)
+inline bool one_line_shape(cryo_dtype dt, int rpl) { return dt == CRYO_F32 && rpl <= 10; }
+int balanced_lpw(int nz, int wpl);
 inline bool shape_built(int rpl, int wpl) {
 #define CRYO_SHAPE_EQ(RP, GW) if (rpl == RP && wpl == GW) return true;
     CRYO_FOR_SHAPES(CRYO_SHAPE_EQ)
@@ -238,7 +241,8 @@ int step_multi(const cryo_plan *p);             // steps one launch may take (1:
 cryo_status launch_steps(const cryo_plan *p, const void *Tin, void *Tout, int K, const double *X,
                          double *partial, int *flag, hipStream_t s);
 int surf_cols(const cryo_plan *p);              // partial sums of the surface mean per step
-int surf_chunk(const cryo_plan *p);             // steps per reduction of them
+int surf_grid(const cryo_plan *p);              // workgroups a workspace holds SURF_CHUNK sums of
+int surf_chunk(const cryo_plan *p);             // steps per reduction of the sums
 size_t step_lds(const cryo_plan *p);            // dynamic LDS of the stepping kernel
 // what a plan is accepted against: the LDS its shape and domain would take
 // with power tables of either kind (laws may be replaced after the check)
