@@ -114,6 +114,25 @@ __device__ inline double surf_weight(const StepArgs<double> &a, int j) {
     else return a.wz_mid;
 }
 
+// One value per row of a line, dealt to a workgroup's threads (row q of thread
+// t, t + 512, ...): a workgroup's slot of running row sums.  Each pass loads its
+// slots' old values well before it adds to them: waited for at the end they
+// cost about 2k cycles at each of the three sums.  (Plain loads and stores; the
+// slot has no other writer, and atomic adds, which need no old value, are not
+// defined on every memory that a workspace may lie in.)
+template <int RPL, int G>
+struct SlotRows {
+    static constexpr int NP = RPL * WAVE * G, T = ADJ_WAVES * WAVE, N = (NP + T - 1) / T;
+    double v[N];
+    __device__ inline void load(const double *slot) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int q = threadIdx.x + i * T;
+            v[i] = q < NP ? slot[q] : 0.0;
+        }
+    }
+};
+
 // What pass 2 of a step hands to pass 1 of the step before, one line per
 // group: lam^{n+1}, X = T^{n+1} (pass 2's own field), and T^n, whose loads are
 // issued with pass 2's (with the chunk-end neighbours of both).
@@ -152,6 +171,17 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
     double *accW = tb.sums + (size_t)wv * RPL * WAVE + lane;
     double *accE = accW + (size_t)ADJ_WAVES * RPL * WAVE;
     double gS = 0.0;
+    // this workgroup's running sums, loaded before the last pass over the rows
+    // where registers allow it
+    double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np, *accg = d.accg + 2 * blockIdx.x;
+    SlotRows<RPL, G> oldW, oldE;
+    double2 oldG;
+    auto load_old = [&] {
+        oldW.load(acc);
+        oldE.load(acc + a.np);
+        oldG = *(const double2 *)accg;
+    };
+    constexpr bool EARLY = KEEP && SlotRows<RPL, G>::N <= 2;
 #pragma unroll
     for (int r = 0; r < RPL; ++r) accW[r * WAVE] = accE[r * WAVE] = 0.0;
     for (int it = 0; it < (KEEP ? 1 : a.lpw); ++it) {
@@ -320,6 +350,7 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
         }
         double qePrev, qwNext;
         nb_exchange<G>(qeL, qwF, qePrev, qwNext, lane, wig, xb[grp]);
+        if constexpr (EARLY) load_old();
         if (active) {
             // one pass over the rows: row r's coupling into row r-1 completes
             // row r-1, which is stored one row late
@@ -375,19 +406,19 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
             d.lpart[base + (RPL - 1) * NL + lg] = lp_prev - qwNext;
         }
     }
+    if constexpr (!EARLY) load_old();
     // heater sums: lane-order tree inside each wave
     double v = gS;
     for (int s = WAVE / 2; s >= 1; s >>= 1) v += __shfl_down(v, s, WAVE);
     __shared__ double gsum[ADJ_WAVES];
     if (lane == 0) gsum[wv] = v;
     __syncthreads();
-    // this workgroup's running sums (one slot per workgroup: no other writer,
-    // the order is fixed; an atomic add only spares waiting for the old value,
-    // about 2k cycles at each of the kernel's three sums), its line groups
-    // added in a fixed order
+    // the line groups' sums in a fixed order, then the slot's
     const double *accL = tb.sums;
-    double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np;
-    for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
+#pragma unroll
+    for (int i = 0; i < SlotRows<RPL, G>::N; ++i) {
+        const int q = threadIdx.x + i * SlotRows<RPL, G>::T;
+        if (q >= SlotRows<RPL, G>::NP) break;
         const int r = q / NL, lq = q % NL, w0 = lq / WAVE, ln = lq % WAVE;
         double sw = 0.0, se = 0.0;
         for (int g = 0; g < NG; ++g) {
@@ -395,14 +426,17 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
             sw += accL[o];
             se += accL[(size_t)ADJ_WAVES * RPL * WAVE + o];
         }
-        unsafeAtomicAdd(acc + q, sw);
-        unsafeAtomicAdd(acc + a.np + q, se);
+        acc[q] = oldW.v[i] + sw;
+        acc[a.np + q] = oldE.v[i] + se;
     }
     if (threadIdx.x == 0) {
         double tot = 0.0;
         for (int w = 0; w < ADJ_WAVES; ++w) tot += gsum[w];
-        unsafeAtomicAdd(d.accg + 2 * blockIdx.x, tot * d.xs * d.s);
-        unsafeAtomicAdd(d.accg + 2 * blockIdx.x + 1, tot * a.pulse.amplitude * d.ds);
+        {
+#pragma clang fp contract(off)                    // (the products rounded, then added)
+            accg[0] = oldG.x + tot * d.xs * d.s;
+            accg[1] = oldG.y + tot * a.pulse.amplitude * d.ds;
+        }
     }
 }
 
@@ -414,22 +448,29 @@ __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj1(StepArgs<double> a, Ad
     adj1_body<RPL, G, CUBE, false, STEPPED, POLY>(a, d, tb, none);
 }
 
-// A workgroup's axial row sums: its line groups added in a fixed order.
+// A workgroup's axial row sums: its line groups added in a fixed order, then
+// the slot's value so far (old).
+__device__ inline double *adj2_slot(const StepArgs<double> &a, const AdjArgs &d) {
+    return d.acc + (size_t)blockIdx.x * 3 * a.np + 2 * a.np;
+}
 template <int RPL, int G>
 __device__ inline void adj2_sums(const StepArgs<double> &a, const AdjArgs &d, double *sums,
-                                 const double (&accZ)[RPL]) {
+                                 const double (&accZ)[RPL], const SlotRows<RPL, G> &old) {
     constexpr int NL = WAVE * G, NG = ADJ_WAVES / G;
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
 #pragma unroll
     for (int r = 0; r < RPL; ++r) sums[(size_t)wv * RPL * WAVE + r * WAVE + lane] = accZ[r];
     __syncthreads();
-    double *acc = d.acc + (size_t)blockIdx.x * 3 * a.np + 2 * a.np;
-    for (int q = threadIdx.x; q < a.np; q += ADJ_WAVES * WAVE) {
+    double *acc = adj2_slot(a, d);
+#pragma unroll
+    for (int i = 0; i < SlotRows<RPL, G>::N; ++i) {
+        const int q = threadIdx.x + i * SlotRows<RPL, G>::T;
+        if (q >= SlotRows<RPL, G>::NP) break;
         const int r = q / NL, lq = q % NL, w0 = lq / WAVE, ln = lq % WAVE;
         double sz = 0.0;
         for (int g = 0; g < NG; ++g)
             sz += sums[(size_t)(g * G + w0) * RPL * WAVE + (size_t)r * WAVE + ln];
-        unsafeAtomicAdd(acc + q, sz);
+        acc[q] = old.v[i] + sz;
     }
 }
 
@@ -453,6 +494,9 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
     // carried from the previous line of the group: the face (j-1, j) flux
     // F = lam (T_j - T_{j-1}) and dF/dT_j; and the lines j, j-1 (T, Y)
     double cF[RPL], cdF[RPL], Tc[RPL], Yc[RPL], Ys[RPL];
+    SlotRows<RPL, G> old;
+    constexpr bool EARLY = SlotRows<RPL, G>::N <= 2;         // (registers)
+    if constexpr (EARLY) old.load(adj2_slot(a, d));
     // groups past the last line read line nz-2 and do no line
     const int jb = min(j0, a.nz - 2);
     const size_t bb = (size_t)jb * LS;
@@ -540,7 +584,8 @@ __device__ inline void adj2_body(const StepArgs<double> &a, const AdjArgs &d,
             Tc[r] = Tn[r];
         }
     }
-    adj2_sums<RPL, G>(a, d, tb.sums, accZ);
+    if constexpr (!EARLY) old.load(adj2_slot(a, d));
+    adj2_sums<RPL, G>(a, d, tb.sums, accZ, old);
 }
 
 // Pass 2 of a group's single line: both faces of a row at once (two law
@@ -588,6 +633,8 @@ __device__ inline void adj2_line(const StepArgs<double> &a, const AdjArgs &d,
         k.XwF = d.T[base + qW];
         k.XeL = d.T[base + qE];
     }
+    SlotRows<RPL, G> old;
+    old.load(adj2_slot(a, d));
     const bool low = active && j == 1, high = active && j == a.nz - 2;
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
@@ -630,7 +677,7 @@ __device__ inline void adj2_line(const StepArgs<double> &a, const AdjArgs &d,
         }
         if (r & 1) __builtin_amdgcn_sched_barrier(0);        // register pressure
     }
-    adj2_sums<RPL, G>(a, d, tb.sums, accZ);
+    adj2_sums<RPL, G>(a, d, tb.sums, accZ, old);
 }
 
 template <int RPL, int G, bool STEPPED, bool POLY = false>
