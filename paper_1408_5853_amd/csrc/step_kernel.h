@@ -28,10 +28,15 @@ namespace cryo {
 // Rows per lane from which a scheduling barrier follows every row.
 constexpr int ROW_FENCE = 10;
 
-// Couplings that the step's line solves leave out (solve_tail): 2^-17 of the
-// type's rounding, of the largest increment on the line.
+// Couplings that the step's line solves leave out (solve_tail), of the largest
+// increment on the line: below the last place that any temperature beside it is
+// held to.  FP64: 2^-17 of its rounding.  FP32 pairs: temperatures lie in
+// [2^-4, 2^20) K, so no increment exceeds 2^20 K, and the smallest are held to
+// 2^-52 K (in the residual).  A pass squares the couplings, so 2^-41, a float's
+// rounding and not the pair's, saves a pass at most (1 to 3 % of a step), and
+// cost the quiet rows beside a hot layer up to 200 times their last place.
 template <typename R>
-constexpr R STEP_DROP = sizeof(R) == 8 ? (R)0x1p-70 : (R)0x1p-41;
+constexpr R STEP_DROP = sizeof(R) == 8 ? (R)0x1p-70 : (R)0x1p-74;
 
 // A barrier that orders LDS accesses only: loads of the next lines stay in
 // flight across it.
