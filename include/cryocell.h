@@ -498,8 +498,9 @@ cryo_status cryo_batch_workspace_bytes(const cryo_batch *batch, size_t *bytes);
 /* Fill every instance's field with its T_init. */
 cryo_status cryo_batch_init(const cryo_batch *batch, void *T, void *stream);
 /* Advance every instance by nsteps steps from global step k0.  The captured
- * graph is tied to `ws`; a call with another workspace re-captures it.
- * Asynchronous on `stream`.  No device allocation after the first call. */
+ * graph is tied to `ws`; a call with another workspace waits for the batch's
+ * previous call and re-captures it.  Otherwise asynchronous on `stream`.
+ * No device allocation after the first call. */
 cryo_status cryo_batch_forward(cryo_batch *batch, void *T, int64_t k0, int64_t nsteps,
                                void *ws, size_t ws_bytes, void *stream);
 /* After a cryo_batch_forward: CRYO_ERR_NONFINITE if an instance produced a

@@ -51,6 +51,9 @@ struct cryo_batch {
     void *graph_ws = nullptr;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
+    // end of the last call's device work: the device block and the graph belong
+    // to it until then
+    hipEvent_t done = nullptr;
 };
 
 namespace cryo {
@@ -74,6 +77,25 @@ cryo_status launch_batch_convert(cryo_dtype dt, bool in, const BatchConv *inst,
                                  int par, hipStream_t s);
 cryo_status launch_set_i64(int64_t *ptr, int64_t v, hipStream_t s);
 cryo_status launch_add_i64(int64_t *ptr, int64_t v, hipStream_t s);
+
+// Waits for the batch's last call (a call under capture leaves no event: its
+// replays are the caller's to order before a call with another workspace).
+static cryo_status batch_wait(cryo_batch *b) {
+    if (b->done && hipEventSynchronize(b->done) != hipSuccess)
+        return fail(CRYO_ERR_DEVICE, "waiting for the batch's previous call");
+    return CRYO_OK;
+}
+
+// Marks the end of a call on stream s, however it returns.
+struct CallEnd {
+    cryo_batch *b;
+    hipStream_t s;
+    ~CallEnd() {
+        hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &c) == hipSuccess && c == hipStreamCaptureStatusNone)
+            (void)hipEventRecord(b->done, s);
+    }
+};
 
 static void batch_free_graph(cryo_batch *b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
@@ -251,7 +273,9 @@ cryo_status cryo_batch_create_with(int32_t n, const cryo_problem *probs, cryo_dt
 
 void cryo_batch_destroy(cryo_batch *b) {
     if (!b) return;
+    (void)batch_wait(b);
     batch_free_graph(b);
+    if (b->done) (void)hipEventDestroy(b->done);
     if (b->d_block) (void)hipFree(b->d_block);
     for (cryo_plan *p : b->plans) cryo_plan_destroy(p);
     delete b;
@@ -298,9 +322,16 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
         hipError_t e = hipMalloc(&b->d_block, b->block_bytes);
         if (e != hipSuccess) return fail(CRYO_ERR_DEVICE, "batch descriptor block");
     }
+    if (!b->done && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
+        b->done = nullptr;
+        return fail(CRYO_ERR_DEVICE, "batch event");
+    }
     // descriptors point into this workspace: refresh them (and the graph)
-    // when the workspace moves
+    // when the workspace moves, once the previous call no longer reads them
+    // (the upload waits for blocking streams only)
     if (b->graph_ws != ws) {
+        const cryo_status st = batch_wait(b);
+        if (st != CRYO_OK) return st;
         batch_free_graph(b);
         const size_t ds = step_desc_bytes(b->dtype);
         for (Bucket &bk : b->buckets)
@@ -321,6 +352,7 @@ cryo_status cryo_batch_forward(cryo_batch *b, void *T, int64_t k0, int64_t nstep
                                  hipMemcpyHostToDevice);
         if (e != hipSuccess) return fail(CRYO_ERR_DEVICE, "batch descriptor upload");
     }
+    const CallEnd end{b, s};
     int64_t *k0p = (int64_t *)(w + counter_off(b));
     auto convert = [&](bool in, int par) {
         const char *blk = (const char *)b->d_block;
