@@ -245,7 +245,8 @@ __device__ inline void adj1_body(const StepArgs<double> &a, const AdjArgs &d,
             // rows in the stepping kernel's scaled form: an interface row's
             // west coefficient is the ratio law at the node and its east one
             // h_i; boundary rows have their unit or zero laws folded into gw,
-            // ge (slot 2 is the unit law there, the zero law on padding)
+            // ge (slot 2 is the unit law there; padding rows are capacity rows
+            // with gw = ge = 0, whose y is zero)
             double l2v = l2 == law_unit(a.L) ? 1.0 : 0.0;
             if ((a.m.iface >> r) & 1) {                      // (uniform)
                 double va = law.lawc(l2, t);

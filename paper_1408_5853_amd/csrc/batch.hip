@@ -196,7 +196,8 @@ using namespace cryo;
 //     9 FP64             2729  2740  1844  1797  1791
 //     24 FP64            3964  3984  3828  3401  3398
 //     64 FP64            9168  9176  9217  9180  9072
-//     160 FP32 pairs    11675 11850 11775 11791 12580
+// The design sweep's first cells at 4, 2 and 1 lines (* taken): 160 FP32 pairs
+// 9672*, 10202, 9941; 64 FP64 6521, 6803*, 6183; 24 FP64 3023, 2594, 2203*.
 static int batch_lpw(const std::vector<cryo_plan *> &plans) {
     for (int lpw = BATCH_LPW; lpw > 1; lpw /= 2) {
         int64_t wg = 0;

@@ -213,13 +213,14 @@ static int multi_grid(const cryo_plan *p, int K) {
 // saves launches (2.4 us each with the latency of the tables and lines).  As
 // many as leave at most one workgroup per unit; us per step at 1, 2, 3, 4
 // steps, 512 rows (FP64 | FP32):
-//     514 lines   8.2  6.7  6.2  6.0    | 5.3  3.9  3.5  3.3   (4 taken)
-//     1026        8.3  6.9  6.4  11.3   | 5.5  4.1  3.6  5.0   (3)
-//     1538        8.6  7.0  11.7  16.6  | 5.8  4.3  5.1  7.0   (2)
-//     2050        8.9  12.7  11.9  21.9 | 6.2  6.0  5.4  8.8   (1 | 3)
+//     514 lines   8.1  6.6  6.1  5.9    | 5.5  4.2  3.7  3.5   (4 taken)
+//     1026        8.3  6.8  6.3  11.2   | 5.8  4.4  3.8  5.1   (3)
+//     1538        8.7  7.0  11.6  16.5  | 6.1  4.6  5.5  7.4   (2)
+//     2050        8.9  12.6  11.8  21.9 | 6.5  6.2  5.6  9.2   (1 | 3)
 // FP32 with short chunks fits two workgroups on a unit: three steps gain up to
-// 27 % there (128 rows: 3.9 -> 2.9), 10 rows per lane lose 20 % (7.6 -> 8.7,
-// general laws); two steps at 2050 to 3074 lines gain nothing.
+// 25 % there (128 rows: 4.1 -> 3.1), 10 rows per lane lose 15 % (7.9 -> 9.1,
+// general laws).  Beyond, at 3074 lines, two steps would gain too (8.5 -> 6.5 at
+// 8 rows per lane, 10.8 -> 10.0 at 10); the rule does not take them.
 int step_multi(const cryo_plan *p) {
     if (!step_shared(p) || p->wpl != 1 || p->rpl > 10 || multi_lds(p) > MAX_STEP_LDS) return 1;
     for (int K = MULTI_MAX; K > 1; --K)

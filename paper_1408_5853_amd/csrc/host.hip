@@ -208,12 +208,12 @@ int balanced_lpw(int nz, int wpl) {
 
 // Lines per wave.  FP32 pairs: one (step_shared; two or more workgroups share
 // a compute unit and take turns with memory and arithmetic) up to 10 rows per
-// lane, on any grid: 512 x 4098 9.1 us a step against 10.2 with 2 lines, 512 x
-// 8194 14.2 against 16.6 and 18.6 (2, 4 lines), 640 x 4098 11.6 against 11.4.
+// lane, on any grid: 512 x 4098 9.4 us a step against 10.9 with 2 lines, 512 x
+// 8194 14.8 against 17.5 and 19.5 (2, 4 lines), 640 x 4098 11.9 against 11.7.
 // Otherwise balanced over the units, so that every unit works and each line
-// group amortises its start-up line: FP64 512 x 4098 14.3, 14.1, 21.4 us (1, 2,
-// 4 lines), 640 x 4098 18.7, 17.0, 26.2, 1024 x 4096 29.1, 23.9, 41; FP32 1024
-// x 4096 16.9, 16.5, 28.
+// group amortises its start-up line: FP64 512 x 4098 14.1, 14.5, 22.3 us (1, 2,
+// 4 lines), 640 x 4098 18.4, 17.3, 27.2, 1024 x 4096 29.1, 24.2, 38; FP32 1024
+// x 4096 16.7, 16.7, 24.5.
 static int pick_lpw(int nz, int rpl, int wpl, cryo_dtype dtype) {
     return one_line_shape(dtype, rpl) ? 1 : balanced_lpw(nz, wpl);
 }

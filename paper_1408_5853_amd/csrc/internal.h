@@ -68,14 +68,15 @@ __host__ __device__ inline uint32_t info_pack(uint32_t kind, uint32_t heat, uint
            (law3 << 18) | (lawC << 24);
 }
 
-// The stepping kernel reads no row words: rows other than capacity rows are
-// found from a lane's word (its chunk's first law, and one bit per row) and
-// by position.  Bits 0..rpl-1 stand for the rows of a chunk.
+// The stepping kernel's one-line form (step_shared) reads no row words (its
+// form for line blocks and the adjoint do): rows other than capacity rows are
+// found from a lane's word (its chunk's first law, and one bit per row) and by
+// position.  Bits 0..rpl-1 stand for the rows of a chunk.
 struct LaneWord {
     uint32_t law;        // radial law of the interval west of the chunk's first row
     uint32_t iface;      // interface rows
     uint32_t heat;       // heater capacity rows
-    uint32_t pad;
+    uint32_t unused;     // (16 bytes)
 };
 // The same bits of any lane of a line (the rows that need a look at all).
 struct RowMasks {

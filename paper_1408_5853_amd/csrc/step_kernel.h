@@ -107,13 +107,14 @@ __device__ inline int own_rows(const StepArgs<R> &a, int wig) {
 // Nothing is decoded per row: a capacity row, by far the most common, takes
 // its two faces from one law, whose constants stay in registers from row to
 // row; interface rows are found from a bit per row and lane, walls and the
-// terminal by position.  Up to 8 FP64 rows per lane (any FP32 shape) that
-// fits 128 registers, and two or more workgroups share a compute unit: one
-// loads its lines while another computes.  One line per wave
-// either way, step_march -> here: 512 x 2048 FP64 10.1 -> 9.1 us a step, FP32
-// 7.9 -> 6.3, 631 x 1201 FP64 11.3 -> 9.9, 1024 x 2050 17.3 -> 14.9; against
-// step_march with several lines: 512 x 8194 FP32 18.6 -> 14.1.  16 FP64 rows
-// take 180 registers and 110 KB, one workgroup per unit, and step_march's
+// terminal by position.  Any FP32 shape fits 128 registers that way, and FP64
+// with the cube or polynomial laws up to 8 rows per lane (general laws up to 7:
+// 130 at 8 rows), so that two or more workgroups share a compute unit: one loads
+// its lines while another computes.  One line per wave either way, step_march ->
+// here: 512 x 2048 FP64 9.2 -> 9.1 us a step, FP32 7.2 -> 6.6, 631 x 1201 FP64
+// 10.6 -> 9.8, 1024 x 2050 15.8 -> 15.0, 512 x 8194 FP64 32.1 -> 23.4; against
+// step_march with 2 and 4 lines: 512 x 8194 FP32 17.5, 19.5 -> 14.8.  16 FP64
+// rows take 184 registers and 110 KB, one workgroup per unit, and step_march's
 // blocks win there once there are more lines than waves (pick_lpw).
 //
 // MULTI (one wave per line): K steps in one launch.  A workgroup owns the
@@ -725,7 +726,8 @@ __device__ inline void step_march(const StepArgs<R> &a, const int blk, const R *
             // slot 2: the north axial face of a capacity row (the row's radial
             // law: capacity rows are scaled by eta^2), the ratio of the inner
             // to the outer layer's law at an interface node (its row divided
-            // by the outer law), or unit / zero (boundary, padding)
+            // by the outer law), or unit (boundary, a terminal line past its
+            // wall)
             R lam2 = law.lawm(l2, T + (cap ? Tnr : T));
             if constexpr (POLY) lam2 = lam2 / law.lawm((inf_r >> 18) & 63, T + T);
             R rc;
