@@ -691,10 +691,11 @@ __global__ __launch_bounds__(ADJ_WAVES *WAVE) void k_adj2(StepArgs<double> a, Ad
 // Bound by a workgroup's chain: 42k cycles on 512 x 2048 with two waves per
 // SIMD (loads of the three lines 5k, axial rows 6k, its sums 4.6k, radial rows
 // 5k, solve 2k, last pass 6k, sums 4.4k), 17 of its 21 us also on a grid of a
-// quarter the lines.  26.5 us a step before the sums were atomic adds, both
-// faces of a row one pass and the field passed on in registers; the laws of a
-// line as a loop of their own before its rows took the general-law kernels
-// from 248 spilled bytes per lane to none.
+// quarter the lines.  26.5 us a step before the sums stopped waiting for the
+// slot's old values, both faces of a row became one pass and the field was
+// passed on in registers.  The laws of a line are a loop of their own before
+// its rows: without it the general-law kernels spilled; now only the (8, 4)
+// ones do (36 to 60 bytes per lane).
 // Pass 2 of step k and pass 1 of step k - 1 in one launch: each line group
 // finishes lam^k of its lines (in registers for one line per group, else
 // written to memory and read back by the same lanes), then runs the next
