@@ -116,3 +116,26 @@ def test_gradient(kind, shape):
     scale = np.max(np.abs(go * th))
     assert scale > 0.0
     assert np.max(np.abs(gg - go) * th) < 1e-8 * scale
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lines", [1, 2])
+def test_batch(lines, dtype):
+    import torch
+
+    import paper_1408_5853_amd as P
+    kinds = ["top", "low", "poly", "warm"]
+    say("case padding batch, %d lines per wave, %s" % (lines, dtype))
+    cases = [_case(k) for k in kinds]
+    b = P.Batch([c for c, _ in cases], dtype, shapes=[(2, 1, lines)] * len(cases))
+    T, ws = b.init(), b.workspace()
+    for i, (c, T0) in enumerate(cases):
+        if T0 is not None:
+            b.field(T, i).copy_(P.Plan(c, dtype).field_from(T0))
+    b.forward(T, 0, NSTEPS, ws=ws)
+    b.poll(ws)
+    torch.cuda.synchronize()
+    for i, (c, T0) in enumerate(cases):
+        To = oracle.forward(c, T=T0, nsteps=NSTEPS)
+        e = np.abs(P.Plan.field_values(b.field(T, i)) - To)
+        assert np.max(e / To) < 1e-10 if dtype == "f64" else np.max(e) < 1e-4, kinds[i]
